@@ -327,7 +327,7 @@ sj_status sj_run_adam(sj_handle h, void *const *ptrs, int nptrs, int64_t step,
 /* The MLP backward pass of an SJ_MLP_BWD handle, as sj_run computes it, for
  * callers that cannot allocate: code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation.  ptrs = {theta, X, t, grad, loss}
- * as for sj_run without the workspace: the per-row activations and deltas go
+ * as for sj_run without the workspace: the workgroups' partial gradients go
  * to a static device array of 1,048,576 floats (4 MiB) that each device this
  * library runs on holds until the process ends.  Requires rows * (4 width + 2)
  * <= 1,048,576 (else SJ_ERR_INVALID_ARG, nothing launched).  Calls no

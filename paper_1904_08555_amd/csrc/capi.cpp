@@ -372,14 +372,14 @@ static void contraction_bytes(const SpecKey &k, size_t *bytes)
 sj_status launch_mlp_bwd(const sj_handle_ *h, void *th, void *X, void *t, void *g, void *loss, void *ws,
                          hipStream_t st)
 {
-    // per-row activations and deltas into ws, then one thread per parameter (and one for the
-    // loss) summing over the rows; every workspace value is written before it is read
-    const size_t P = (size_t)mlp_nparams(h->key.inputs, h->key.width);
-    void *args1[] = {&th, &X, &t, &ws};
+    // one workgroup writes the gradient itself; more write partial gradients into ws, which the
+    // second launch sums (every workspace value is written before it is read)
+    void *args1[] = {&th, &X, &t, &ws, &g, &loss};
     hipError_t e = hipModuleLaunchKernel(h->fn, h->geom.grid, 1, 1, h->geom.block, 1, 1, 0, st, args1, nullptr);
     if (e != hipSuccess) return fail(SJ_ERR_LAUNCH, std::string("hipModuleLaunchKernel: ") + hipGetErrorString(e));
-    void *args2[] = {&X, &ws, &g, &loss};
-    const unsigned grid2 = (unsigned)((P + 1 + 255) / 256);
+    if (h->geom.grid == 1) return SJ_OK;
+    const unsigned grid2 = (unsigned)((mlp_nparams(h->key.inputs, h->key.width) + 1 + 63) / 64);
+    void *args2[] = {&ws, &g, &loss};
     e = hipModuleLaunchKernel(h->fn2, grid2, 1, 1, 256, 1, 1, 0, st, args2, nullptr);
     if (e != hipSuccess) return fail(SJ_ERR_LAUNCH, std::string("hipModuleLaunchKernel: ") + hipGetErrorString(e));
     return SJ_OK;

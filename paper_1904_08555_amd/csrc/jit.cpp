@@ -131,6 +131,10 @@ static void layout_view(int layout, int64_t Z, int64_t G, int64_t *B, int64_t *I
     }
 }
 
+// rows of the MLP kernels' tiles: 32, so that a minibatch's partial gradients are few, and 16
+// where fewer rows than that are all there is
+static int64_t mlp_tile_rows(int64_t rows) { return rows <= 16 ? 16 : 32; }
+
 static bool valid_block(int b) { return b >= 64 && b <= 1024 && b % 64 == 0; }
 
 static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const char *arch, SpecKey *out);
@@ -654,7 +658,11 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
             key.inputs = s->inputs;
             key.width = s->width;
         }
-        key.block = s->block ? s->block : (k == SJ_ADAM ? 256 : 64);
+        // MLP: one wave per 16x16 C tile of a layer (row tiles x unit blocks), 2 to 8 waves
+        key.block = 256;
+        if (k != SJ_ADAM)
+            key.block = 64 * (int32_t)std::max<int64_t>(2, std::min<int64_t>(8, mlp_tile_rows(s->rows) / 16 * ((s->width + 15) / 16)));
+        if (s->block) key.block = s->block;
         if (!valid_block(key.block)) return fail(SJ_ERR_INVALID_ARG, "block must be a multiple of 64 in [64, 1024]");
         key.order = 1;
         return (*out = key), SJ_OK;
@@ -739,8 +747,16 @@ static bool scattering_persistent(const SpecKey &k)
 Geometry key_geometry(const SpecKey &k)
 {
     Geometry g{0, (unsigned)k.block, 0};
-    if (k.kernel == SJ_MLP_FWD || k.kernel == SJ_MLP_BWD || k.kernel == SJ_ADAM)
-        g.grid = (unsigned)((k.rows + k.block - 1) / k.block);
+    if (k.kernel == SJ_ADAM) g.grid = (unsigned)((k.rows + k.block - 1) / k.block);
+    if (k.kernel == SJ_MLP_FWD || k.kernel == SJ_MLP_BWD) {
+        // a workgroup per tile of rows, at most what the device holds about twice over; the backward
+        // pass' partial gradients have to fit in its workspace of rows * (4 width + 2) floats
+        const int64_t rb = mlp_tile_rows(k.rows), tiles = (k.rows + rb - 1) / rb;
+        int64_t nb = std::min<int64_t>(tiles, 512);
+        if (k.kernel == SJ_MLP_BWD)
+            nb = std::max<int64_t>(1, std::min(nb, k.rows * (4 * k.width + 2) / (mlp_nparams(k.inputs, k.width) + 1)));
+        g.grid = (unsigned)nb;
+    }
     if (k.kernel == SJ_SCATTERING && k.variant == SJ_VAR_MFMA && scattering_nm_inner(k)) {
         g.grid = (unsigned)std::min<int64_t>((k.Z + 15) / 16, 8192);   // one 16-zone block per workgroup
         g.persistent = 1;
@@ -1011,9 +1027,10 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
     if (k.kernel == SJ_MLP_FWD || k.kernel == SJ_MLP_BWD || k.kernel == SJ_ADAM) {
         o << "#define SJ_R " << k.rows << "\n#define SJ_F " << (k.inputs ? k.inputs : 1) << "\n#define SJ_H "
           << (k.width ? k.width : 1) << "\n#define SJ_BLOCK " << k.block << "\n#define SJ_NT_LOAD 0\n#define SJ_NT_STORE 0\n#define SJ_ACCUM 0\n"
-          << "#define SJ_WANT_FWD " << (k.kernel == SJ_MLP_FWD) << "\n#define SJ_WANT_BWD " << (k.kernel == SJ_MLP_BWD)
-          << "\n#define SJ_WANT_ADAM " << (k.kernel == SJ_ADAM) << "\n";
-        body = kTpl_mlp;
+          << "#define SJ_WANT_FWD " << (k.kernel == SJ_MLP_FWD) << "\n#define SJ_WANT_BWD " << (k.kernel == SJ_MLP_BWD) << "\n";
+        if (k.kernel != SJ_ADAM)
+            o << "#define SJ_RB " << mlp_tile_rows(k.rows) << "\n#define SJ_NB " << key_geometry(k).grid << "\n";
+        body = (k.kernel == SJ_ADAM) ? kTpl_adam : kTpl_mlp_net;
         if (k.kernel == SJ_MLP_FWD) {
             *name = "sj_mlp_fwd";
         } else if (k.kernel == SJ_MLP_BWD) {

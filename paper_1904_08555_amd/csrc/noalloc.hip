@@ -2,7 +2,7 @@
 // (sj_run_mlp_bwd_noalloc).
 //
 // The backward pass of the cost model needs a workspace of rows * (4 width + 2)
-// floats (per-row activations and deltas).  sj_run takes it from the caller;
+// floats (its workgroups' partial gradients).  sj_run takes it from the caller;
 // this entry point uses a static device array instead, for callers that cannot
 // allocate (code under HIP graph capture, tight serving loops).  Each device
 // the library runs on holds its own copy of the array, kScratchFloats floats

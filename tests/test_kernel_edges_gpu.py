@@ -1,0 +1,59 @@
+"""Kernel structures at the sizes where their tiling can go wrong (edges of
+tiles, remainders, the smallest and largest of a range), against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1904_08555_amd as P
+    P.sj_init(0)
+    return P
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    oracle.lib()
+    return oracle
+
+
+# rows around the 16- and 32-row tiles and the one-workgroup limit; units and inputs around the
+# 16-wide blocks; the widest network; one wave and sixteen
+@pytest.mark.parametrize("F,H,R,block", [(16, 16, 15, 0), (15, 17, 16, 0), (17, 15, 17, 0), (33, 48, 32, 0), (8, 64, 33, 0),
+                                         (37, 64, 53, 0), (64, 31, 257, 64), (1, 126, 97, 0), (48, 100, 65, 1024),
+                                         (24, 64, 20000, 0)])
+def test_mlp_tiles(P, orc, F, H, R, block):
+    rng = np.random.default_rng(F + H + R)
+    n = orc.mlp_nparams(F, H)
+    theta = (rng.standard_normal(n) * (1.0 / np.sqrt(H))).astype(np.float32)
+    X = rng.standard_normal((R, F)).astype(np.float32)
+    t = rng.standard_normal(R).astype(np.float32)
+    spec = dict(dtype=P.SJ_F32, rows=R, inputs=F, width=H, block=block)
+    th_d, X_d, t_d = dev(theta), dev(X), dev(t)
+    y_d = torch.full((R,), float("nan"), dtype=torch.float32, device="cuda")
+    P.sj_run(P.sj_specialize(P.SJ_MLP_FWD, **spec), [th_d, X_d, y_d])
+    y_ref = orc.mlp_forward(F, H, theta.astype(np.float64), X.astype(np.float64))
+    # FP32: three sums of at most 127 terms of magnitude about 1, gamma_130 = 8e-6 against the outputs' size
+    assert np.abs(host(y_d) - y_ref).max() <= 1e-5 * max(1.0, np.abs(y_ref).max())
+    g_d = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+    loss_d = torch.full((1,), float("nan"), dtype=torch.float32, device="cuda")
+    # the workspace's end is guarded: partial gradients have to stay inside it
+    ws = torch.full((R * (4 * H + 2) + 64,), 7.0, dtype=torch.float32, device="cuda")
+    hb = P.sj_specialize(P.SJ_MLP_BWD, **spec)
+    P.sj_run(hb, [th_d, X_d, t_d, g_d, loss_d, ws])
+    loss_ref, g_ref = orc.mlp_loss_grad(F, H, theta.astype(np.float64), X.astype(np.float64), t.astype(np.float64))
+    g = host(g_d).astype(np.float64)
+    assert (host(ws)[-64:] == 7.0).all()
+    assert abs(float(host(loss_d)[0]) - loss_ref) <= 1e-5 * max(1.0, loss_ref)
+    assert np.linalg.norm(g - g_ref) <= 1e-4 * np.linalg.norm(g_ref)   # the bound of the backward pass' other test
+    g2, l2 = torch.empty_like(g_d), torch.empty_like(loss_d)
+    P.sj_run(hb, [th_d, X_d, t_d, g2, l2, torch.empty_like(ws)])
+    assert torch.equal(g2, g_d) and torch.equal(l2, loss_d)            # a fixed order of summation
