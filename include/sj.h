@@ -280,7 +280,8 @@ sj_status sj_specialize_with_code(sj_kernel k, const sj_spec *spec, const void *
  *                  spec->D = D1D (dofs per direction, 1..32), spec->NM = Q1D (points per direction, 1..32),
  *                  spec->inputs = dim (1, 2, 3), spec->count = NE (elements); B1 row-major [Q1D][D1D] (the
  *                  1-D basis at the points); per element the first index component is fastest; tile_n =
- *                  elements per wave (0 = default).  y_e = B^T diag(D_e) B x_e, B the dim-fold tensor
+ *                  elements per wave (0 = default; hexahedra with Q1D >= 4 other than 6 are taken by
+ *                  whole workgroups by default, and tile_n is then the elements of a workgroup).  y_e = B^T diag(D_e) B x_e, B the dim-fold tensor
  *                  product of B1 (the Laghos-style partial-assembly mass action); overwrites Y.
  *   SJ_MLP_FWD:    {theta f32, X [rows*inputs] f32, y [rows] f32}
  *   SJ_MLP_BWD:    {theta f32, X [rows*inputs] f32, t [rows] f32, grad f32 (same packing as theta), loss [1] f32,

@@ -182,6 +182,40 @@ sj_status make_key(sj_kernel k, const sj_spec *s, int device, const char *arch, 
     return st;
 }
 
+// The workgroup form of the mass operator on hexahedra (mass_pa_hex): elements per workgroup and
+// threads it is taken with by default, false where the other forms stay the default.  Measured on
+// MI355X over D1D 2..18, Q1D D1D..2 D1D - 2 at about 1 GB of elements (floor 191 us at a copy's
+// rate), against the better of the pipelined and the staged form:
+//   Q1D 4, 5: eight elements, 256 threads (D1D=3 Q1D=4 193 us against 218, D1D=4 Q1D=5 184 against 244)
+//   Q1D 7, 8: eight elements, 512 threads (D1D=5 Q1D=8 183 us against 345, D1D=6 Q1D=8 182 against 407)
+//   Q1D 9..14: one element, 128 threads (D1D=9 Q1D=9 217 us against 860, D1D=8 Q1D=12 201 against over 2000);
+//     wider elements need more threads for the registers (D1D=12 Q1D=12 257 us at 256, 821 at 128)
+//   Q1D <= 3 and 6: within 5% of the pipelined form, which stays (D1D=4 Q1D=6 187-200 us against 191-201)
+// Fewer elements per workgroup where the mesh would give less than two workgroups a CU.
+static bool mass_hex_tile(int64_t D, int64_t Q, int64_t ne, int *ew, int *block)
+{
+    if (Q < 4 || Q == 6) return false;
+    int e = Q <= 8 ? 8 : 1, b = Q <= 5 ? 256 : Q <= 8 ? 512 : std::max(D, Q) >= 17 ? 512 : (D >= 10 || Q >= 15) ? 256 : 128;
+    // a thread's x, y and point values in flight, and the LDS of a workgroup
+    auto fits = [&] {
+        const int64_t nx = (e * D * D * D + b - 1) / b, nz = (e * Q * Q + b - 1) / b;
+        const int64_t lds = e * (std::max(D * D * (D | 1), D * Q * Q) + D * D * (Q | 1)) * 8;
+        return 2 * nx + nz * Q <= 56 && lds <= 128 * 1024;
+    };
+    while (e > 1 && (ne < 512 * e || !fits())) { e /= 2; b = std::max(64, b / 2); }
+    while (b < 512 && !fits()) b *= 2;
+    *ew = e;
+    *block = b;
+    return fits();
+}
+
+static bool mass_hex(const SpecKey &k)
+{
+    int ew = 0, block = 0;
+    return k.kernel == SJ_MASS && k.order == 1 && k.inputs == 3 && mass_hex_tile(k.D, k.NM, k.rows, &ew, &block) &&
+           k.tile_n == ew && k.block == block;
+}
+
 static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const char *arch, SpecKey *out)
 {
     if (!s || !out) return fail(SJ_ERR_INVALID_ARG, "null spec or output");
@@ -507,7 +541,17 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
         int block = s->block;
         if (block == 0) block = (order == 2) ? 64 : (lds(128) <= 64 * 1024) ? 128 : 64;
         if (!valid_block(block)) return fail(SJ_ERR_INVALID_ARG, "block must be a multiple of 64 in [64, 1024]");
-        if (lds(block) > 160 * 1024) return fail(SJ_ERR_UNSUPPORTED, "mass operator tiles exceed 160 KiB of LDS");
+        // the hexahedra's workgroup form by default, or where order 1 names its tile and block
+        int hew = 0, hblock = 0;
+        const bool hex = dim == 3 && mass_hex_tile(D1D, Q1D, s->count, &hew, &hblock);
+        const bool hex_named = hex && s->order == 1 && s->tile_n == hew && s->block == hblock;
+        if (!hex_named && lds(block) > 160 * 1024)
+            return fail(SJ_ERR_UNSUPPORTED, "mass operator tiles exceed 160 KiB of LDS");
+        if (hex && s->order == 0 && s->tile_n == 0 && s->block == 0) {
+            order = 1;
+            ew = hew;
+            block = hblock;
+        }
         if (s->count * std::max(nd, nq) > (int64_t(1) << 50)) return fail(SJ_ERR_INVALID_ARG, "arrays too large");
         key.D = D1D; key.NM = Q1D; key.inputs = dim; key.rows = s->count;
         key.tile_n = ew; key.block = block; key.variant = SJ_VAR_DIRECT; key.order = order;
@@ -776,6 +820,10 @@ Geometry key_geometry(const SpecKey &k)
     if (k.kernel == SJ_MASS) {
         const int64_t per_block = (int64_t)(k.block / 64) * k.tile_n;
         g.grid = (unsigned)((k.rows + per_block - 1) / per_block);
+        if (mass_hex(k)) {     // a group of elements per workgroup, persistent
+            g.grid = (unsigned)std::min<int64_t>((k.rows + k.tile_n - 1) / k.tile_n, 65536);
+            g.persistent = 1;
+        }
         if (k.order == 2) {   // persistent: capped at load time to the workgroups the device holds at once
             g.grid = (unsigned)std::min<int64_t>(g.grid, 65536);
             g.persistent = 1;
@@ -970,7 +1018,7 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
           << k.rows << sfx << "\n#define SJ_EW " << k.tile_n << "\n#define SJ_BLOCK " << k.block << "\n#define SJ_NT_LOAD "
           << ((k.flags & SJ_FLAG_LOADS_CACHED) ? 0 : 1) << "\n#define SJ_NT_STORE " << ((k.flags & SJ_FLAG_STORES_CACHED) ? 0 : 1)
           << "\n#define SJ_ACCUM 0\n";
-        body = (k.order == 2) ? kTpl_mass_pa_pipe : kTpl_mass_pa;
+        body = (k.order == 2) ? kTpl_mass_pa_pipe : mass_hex(k) ? kTpl_mass_pa_hex : kTpl_mass_pa;
         *name = std::string(k.order == 2 ? "sj_mass_pa_pipe_" : "sj_mass_pa_") + std::to_string(k.inputs) + "d_d" +
                 std::to_string(k.D) + "_q" + std::to_string(k.NM);
         o << "#define SJ_KERNEL_NAME " << *name << "\n";

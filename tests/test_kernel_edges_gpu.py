@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import dev, host
+from helpers import TOL_F64, componentwise_err, dev, host
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,26 @@ def test_mlp_tiles(P, orc, F, H, R, block):
     g2, l2 = torch.empty_like(g_d), torch.empty_like(loss_d)
     P.sj_run(hb, [th_d, X_d, t_d, g2, l2, torch.empty_like(ws)])
     assert torch.equal(g2, g_d) and torch.equal(l2, loss_d)            # a fixed order of summation
+
+
+# one and several elements a workgroup, a ragged last group, more elements than resident workgroups
+# hold at once (a second round with prefetched loads), each thread count of the default tile
+@pytest.mark.parametrize("D1D,Q1D,NE", [(3, 4, 13), (3, 4, 41003), (1, 7, 700), (5, 8, 4101), (4, 5, 5), (7, 7, 6001), (8, 12, 5),
+                                        (2, 14, 4100), (9, 15, 3), (12, 12, 2), (12, 5, 7), (16, 16, 2), (20, 4, 3)])
+def test_mass_hex_groups(P, orc, D1D, Q1D, NE):
+    rng = np.random.default_rng(D1D * Q1D + NE)
+    B1 = rng.uniform(-1, 1, Q1D * D1D)
+    Dq, X = rng.uniform(0, 1, NE * Q1D ** 3), rng.uniform(-1, 1, NE * D1D ** 3)
+    Y = torch.full((X.size,), float("nan"), dtype=torch.float64, device="cuda")
+    h = P.sj_specialize(P.SJ_MASS, D=D1D, NM=Q1D, inputs=3, count=NE)
+    P.sj_run(h, [dev(B1), dev(Dq), dev(X), Y])
+    r = P.sj_resolve(P.SJ_MASS, D=D1D, NM=Q1D, inputs=3, count=NE)
+    assert r["order"] == 1
+    assert P.sj_specialize(P.SJ_MASS, D=D1D, NM=Q1D, inputs=3, count=NE, order=1, tile_n=r["tile_n"], block=r["block"]) == h
+    # the oracle's direct sum is long: the first and last 300 elements
+    es = np.unique(np.r_[0:min(300, NE), max(0, NE - 300):NE])
+    Ds, Xs = Dq.reshape(NE, -1)[es].ravel(), X.reshape(NE, -1)[es].ravel()
+    got = host(Y).reshape(NE, -1)
+    assert np.isfinite(got).all()
+    assert componentwise_err(got[es].ravel(), orc.mass(3, D1D, Q1D, B1, Ds, Xs),
+                             orc.mass(3, D1D, Q1D, B1, Ds, Xs, absolute=True)) <= TOL_F64
