@@ -101,14 +101,16 @@ typedef enum sj_dtype {
     SJ_F32 = 3      /* MLP kernels */
 } sj_dtype;
 
-/* Kernel structure for LTimes / LPlusTimes.  AUTO picks DIRECT when the
- * innermost storage axis is a column axis (DGZ, DZG, GDZ, ZDG) and the FP64
- * matrix-core row kernel (MFMA) when it is D (GZD, ZGD); BF16 dtypes always
- * use MFMA.  FP64 MFMA with a column axis innermost is the matrix-core column
- * kernel (chosen explicitly, or by a tuner).  The fused SJ_LTIMES_LPLUS has
- * DIRECT and, for D innermost, the MFMA row structure (AUTO's choice there).
- * When AUTO's first choice declines a shape (register or LDS limits), the
- * next structure that accepts it is taken. */
+/* Kernel structure for LTimes / LPlusTimes.  AUTO picks, when the innermost
+ * storage axis is a column axis (DGZ, DZG, GDZ, ZDG), DIRECT for many columns
+ * and few moments and the FP64 matrix-core column kernel (MFMA) otherwise, the
+ * line measured on MI355X (about 131,072 columns, 65,536 where the contiguous
+ * extent is no multiple of 16; any number with more than 48 moments; DIRECT
+ * where a tile field of the spec is set); the FP64 matrix-core row kernel
+ * (MFMA) when it is D (GZD, ZGD); BF16 dtypes always use MFMA.  The fused
+ * SJ_LTIMES_LPLUS has DIRECT and, for D innermost, the MFMA row structure
+ * (AUTO's choice there).  When AUTO's first choice declines a shape (register
+ * or LDS limits), the next structure that accepts it is taken. */
 typedef enum sj_variant {
     SJ_VAR_AUTO = 0,
     SJ_VAR_DIRECT = 1,   /* lanes along the contiguous column axis, direct HBM<->VGPR */
@@ -129,10 +131,13 @@ typedef enum sj_variant {
                                            (phi += L psi, psi' += L+ phi: several direction sets summed into one
                                            output) instead of overwriting; the output is then also read */
 /* Without a loads flag (stores flag) the default measured on MI355X applies:
- * nontemporal stores for every streamed output; nontemporal loads for LTimes'
- * column kernels, ordinary loads for LPlusTimes and for the FP64 MFMA row
- * kernel.  The two flags of a pair exclude each other; every policy flag is
- * part of the specialization key. */
+ * nontemporal stores for LPlusTimes and the row kernels; ordinary stores of
+ * LTimes' moments where they exceed what the caches hold anyway (LPlusTimes
+ * reads them next), and where rows are no multiple of a 128-byte line;
+ * nontemporal loads for LTimes' column kernels and for large LPlusTimes column
+ * kernels, ordinary loads for the FP64 MFMA row kernel.  The two flags of a
+ * pair exclude each other; every policy flag is part of the specialization
+ * key. */
 #define SJ_FLAG_GENERIC_PER_LAYOUT 0x80u /* sj_generic_run, LTimes / LPlusTimes: the kernel compiled ahead of time
                                            for the spec's nesting (sizes still run-time arguments), Kripke's
                                            multiversioning; without it one kernel serves every nesting */

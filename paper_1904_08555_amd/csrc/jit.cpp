@@ -131,9 +131,76 @@ static void layout_view(int layout, int64_t Z, int64_t G, int64_t *B, int64_t *I
     }
 }
 
+static bool cols_flat(const SpecKey &k) { return k.B > 1 && k.I % (16 * k.tile_n) != 0; }
+
+static int64_t cols_tiles(const SpecKey &k)
+{
+    const int64_t cols = 16 * k.tile_n;
+    return cols_flat(k) ? (k.B * k.I + cols - 1) / cols : k.B * ((k.I + cols - 1) / cols);
+}
+
+// FP64 matrix-core columns: few columns.  Each wave then takes one tile and reads the weight
+// fragments it needs straight from memory, beside the input's loads (SJ_WDIRECT), and waves share
+// a tile's 16-output blocks until there are about four waves a CU, at most four blocks each.
+// Measured on MI355X (LTimes / LPlusTimes, D = 128, NM = 64, us, weights through LDS against this):
+// 2,000 columns 14 / 14 against 5.2 / 4.5; 8,000: 15 / 15 against 8.6 / 7.5; 16,384: 16 / 16 against
+// 13 / 12; 32,768: 18 / 20 against 26 / 26 (the weights are read once per 16 or 32 columns).
+// 1 where the form is not taken, also where its registers would not fit.
+static int64_t cols_split(const SpecKey &k, bool *wdirect)
+{
+    *wdirect = false;
+    const int64_t ob = ((k.kernel == SJ_LTIMES ? k.NM : k.D) + 15) / 16;
+    if (k.B * k.I > 16384) return 1;
+    const int64_t want = std::max<int64_t>({1, std::min<int64_t>({4, ob, 1024 / cols_tiles(k)}), (ob + 3) / 4});
+    const int64_t obw = (ob + want - 1) / want, os = (ob + obw - 1) / obw;
+    const int64_t regs = 2 * (2 * k.unroll * (obw + k.tile_n) + 4 * obw * k.tile_n) + 40;
+    if (regs > 512 / std::max(1, k.block / 256)) return 1;
+    *wdirect = true;
+    return os;
+}
+
 // rows of the MLP kernels' tiles: 32, so that a minibatch's partial gradients are few, and 16
 // where fewer rows than that are all there is
 static int64_t mlp_tile_rows(int64_t rows) { return rows <= 16 ? 16 : 32; }
+
+// Column layouts, every tile field left to the library: whether SJ_VAR_AUTO takes the FP64
+// matrix-core column kernel, and the tile it takes (into *mf).  Measured on MI355X (LTimes / LPlusTimes,
+// us, vector-FMA structure against matrix cores), D = 128 NM = 16 unless said otherwise:
+//   2,000 columns 18 / 25 against 4.4 / 3.0; 16,384: 22 / 25 against 7.2 / 5.9; 65,536: 26 / 26 against
+//   14 / 16; 131,072: 34 / 32 against 29 / 30; 524,288: 106 / 109 against 122 / 107.
+// One thread per column or two leaves the chip idle below that and each thread a chain of D NM FMAs fed
+// by scalar loads; a wave per 16 columns does not.  With many columns the vector form is at the memory
+// rate, except for high orders (NM = 64, 2M columns: 820 / 905 against 738 / 742).  Rows that are no
+// multiple of a 128-byte line move the line down (65,535 columns 25 / 18 against 20 / 18), few moments too
+// (NM = 4, D = 48, 65,536 columns: 6.5 / 5.9 against 6.6 / 5.9).  Very short rows (ZDG with up to 8 groups)
+// take the matrix cores at any size: a quarter-wave covers 16 columns whatever record they are in
+// (62,035 zones of 2 groups, D = 27, NM = 9: 12 / 14 against 8.4 / 9.6).  Chains of up to 256 products
+// are done within a launch's time either way.
+static bool cols_mfma_tile(const sj_spec *s, int64_t B, int64_t I, sj_spec *mf)
+{
+    if (I <= 1 || s->tile_n || s->tile_k || s->unroll || s->block || s->order) return false;
+    if (s->D < 1 || s->NM < 1 || s->D > 4096 || s->NM > 4096 || I > (int64_t(1) << 50) / B) return false;
+    const int64_t cols = B * I;
+    const bool ragged = I % 16 != 0, short_rows = B > 1 && I <= 8 && cols > 16384;
+    if (!short_rows) {
+        if (s->D * s->NM <= 256) return false;
+        const int64_t most = (ragged ? 65536 : 131072) / (s->NM < 9 ? 2 : 1);
+        if (cols > most && !(s->NM > 48 && !ragged)) return false;
+    }
+    mf->variant = SJ_VAR_MFMA;
+    mf->unroll = 8;
+    if (cols <= 16384) {   // a wave per workgroup, weights from memory (see cols_split)
+        mf->tile_n = (I % 2 == 0 && cols > 8192) ? 2 : 1;
+        mf->block = 64;
+    } else if (cols <= 131072 || I % 2 != 0) {
+        mf->tile_n = 1;
+        mf->block = 512;
+    } else {
+        mf->tile_n = 2;
+        mf->block = 256;
+    }
+    return true;
+}
 
 static bool valid_block(int b) { return b >= 64 && b <= 1024 && b % 64 == 0; }
 
@@ -143,7 +210,7 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
 // and when that one declines the shape (SJ_ERR_UNSUPPORTED: register, LDS or
 // size limits) the next structure that accepts it, so that every valid shape
 // has a default.  D innermost: MFMA rows, STAGED, DIRECT; a column axis
-// innermost: DIRECT, MFMA columns.
+// innermost: MFMA columns where cols_mfma_tile says so, DIRECT, MFMA columns.
 // LDS bytes of the nm-innermost scattering MFMA form: 16 zones x G runs of NM moments, run pitch
 // NM + 2 (NM + 1 when odd) doubles, zone pitch two doubles more than G runs
 static int64_t scattering_block_lds(int64_t NM, int64_t G)
@@ -166,6 +233,11 @@ sj_status make_key(sj_kernel k, const sj_spec *s, int device, const char *arch, 
     static const int kCols[2] = {SJ_VAR_DIRECT, SJ_VAR_MFMA};
     static const int kFusedRows[2] = {SJ_VAR_MFMA, SJ_VAR_DIRECT};
     static const int kFusedCols[1] = {SJ_VAR_DIRECT};
+    sj_spec mf = *s;
+    if (k != SJ_LTIMES_LPLUS && cols_mfma_tile(s, B, I, &mf)) {
+        const sj_status st = make_key_one(k, &mf, device, arch, out);
+        if (st != SJ_ERR_UNSUPPORTED) return st;
+    }
     const int *order = (I == 1) ? kRows : kCols;
     int n = (I == 1) ? 3 : 2;
     if (k == SJ_LTIMES_LPLUS) {
@@ -298,8 +370,10 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
             // Accumulators (LTimes) or moments (LPlusTimes, both for the fused kernel) live in registers.
             const int64_t regs = s->NM * vec;
             if (regs > 128) return fail(SJ_ERR_UNSUPPORTED, "NM * tile_n > 128 FP64 values per thread");
-            // Full unrolling while the straight-line body stays moderate (the fused kernel has two phases).
-            key.full_unroll = (red * outn * vec * (k == SJ_LTIMES_LPLUS ? 2 : 1) <= 4096) ? 1 : 0;
+            // Full unrolling while the straight-line body stays moderate (the fused kernel has two phases):
+            // 2400 FMAs of it miss the instruction cache (LTimes and LPlusTimes, GDZ 16384 x 30, D = 104,
+            // NM = 25: 317 us against 195 us rolled; D = 48, NM = 9, under the line, 81 us either way).
+            key.full_unroll = (red * outn * vec * (k == SJ_LTIMES_LPLUS ? 2 : 1) <= 1024) ? 1 : 0;
             key.tile_k = 0;
             // Rotation pays when consecutive rows are >= 1 MiB apart (measured on MI355X:
             // 8 MiB row stride, 5.35 TB/s ascending vs 6.2 TB/s rotated).
@@ -836,9 +910,9 @@ Geometry key_geometry(const SpecKey &k)
         } else if (k.variant == SJ_VAR_STAGED) {
             g.grid = (unsigned)((k.B + k.tile_n - 1) / k.tile_n);
         } else if (k.variant == SJ_VAR_MFMA && k.dtype == SJ_F64 && k.I > 1) {
-            const int64_t tiles = k.B * ((k.I + 16 * k.tile_n - 1) / (16 * k.tile_n));
-            const int64_t waves = k.block / 64;
-            g.grid = (unsigned)std::min<int64_t>((tiles + waves - 1) / waves, 2048);
+            bool wdirect = false;
+            const int64_t items = cols_tiles(k) * cols_split(k, &wdirect), waves = k.block / 64;
+            g.grid = (unsigned)std::min<int64_t>((items + waves - 1) / waves, 2048);
         } else if (k.variant == SJ_VAR_MFMA && k.dtype == SJ_F64 && k.kernel == SJ_LTIMES_LPLUS) {
             // persistent: at most one group of tiles per wave; capped at load time to the
             // workgroups the device holds at once
@@ -904,11 +978,10 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
 {
     // streaming hint: skip cache retention when every fetched line is used at once.
     // Explicit flags, else the default measured on MI355X at Z=32768 G=32 D=96 NM=16:
-    // nontemporal stores for every streamed output; nontemporal loads for LTimes' column
-    // kernels (LTimes DGZ 166 us vs 177 us with ordinary loads) and its LDS-staged row kernel
-    // (163 us vs 174 us); ordinary loads for LPlusTimes (DGZ 151 us vs 186 us nontemporal) and
-    // for the direct row kernels, whose lanes read each 128-byte line in two halves (171 us vs
-    // 199 us).
+    // nontemporal stores for every streamed output (columns: below); nontemporal loads for
+    // LTimes' column kernels (LTimes DGZ 166 us vs 177 us with ordinary loads) and its LDS-staged
+    // row kernel (163 us vs 174 us); ordinary loads for LPlusTimes' row kernels and for the direct
+    // row kernels, whose lanes read each 128-byte line in two halves (171 us vs 199 us).
     // The BF16 row form reads and writes every 128-byte line in two 64-byte halves from two
     // instructions: with nontemporal hints the halves travel separately (measured by the HBM
     // counters at Z=262144 G=64 D=128 NM=64: 10.2 GB read and 4.7 GB written against 8.6 and
@@ -919,6 +992,31 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
     const bool streamed = (k.variant != SJ_VAR_DIRECT) || k.I * (k.tile_n ? k.tile_n : 1) >= 16;
     int ntl = ((k.kernel == SJ_LTIMES || k.kernel == SJ_LTIMES_LPLUS) && streamed && !direct_rows && !bf16_rows) ? 1 : 0;
     int nts = (streamed && !bf16_rows) ? 1 : 0;
+    // FP64 columns.  LTimes stores the moments that LPlusTimes reads next: ordinary stores keep them in
+    // the last-level cache, from where LPlusTimes takes them with nontemporal loads (pairs, us, nontemporal
+    // stores and ordinary loads against these: DGZ 32768 x 32, D = 96, NM = 16 347 / 320; 20000 x 32, NM = 36
+    // 296 / 257; DZG 64000 x 32, D = 128, NM = 64 1432 / 1389); arrays of up to 32 MB stay in the caches
+    // either way (29 MB: 9.6 / 9.5).
+    // Rows that are no multiple of a 128-byte line: pieces that share a line come from different
+    // instructions or waves, so ordinary stores (ZDG 16,312 zones of 41 groups, D = 120, NM = 36 540 / 490;
+    // GDZ rows of 8,671, D = 112, NM = 4 40.5 / 33.3; matrix cores, ZDG 1,387 x 47, D = 72, NM = 16 43 / 25),
+    // but not where LPlusTimes writes longer rows that the caches hold (DGZ 46,341 columns, D = 112, NM = 4
+    // 18.6 nontemporal, 24.8 ordinary), forms them from many moments (GDZ rows of 30,010, D = 96, NM = 25
+    // 158 / 198) or in 16-byte pieces of middling rows (GDZ rows of 6,330, D = 80, NM = 16 97 / 109; of
+    // 30,882, D = 112 231 / 217).  The matrix-core form reads ragged rows in 128-byte pieces: ordinary loads.
+    if (k.dtype == SJ_F64 && k.I > 1 && (ntl || nts)) {
+        const bool ragged = k.I % 16 != 0, mfma = k.variant == SJ_VAR_MFMA, lt = k.kernel == SJ_LTIMES;
+        const bool big = 8 * k.B * k.I * (k.D + k.NM) > (int64_t(32) << 20);
+        if (!ragged) {
+            if (lt && big) nts = 0;
+            if (k.kernel == SJ_LPLUSTIMES && big) ntl = 1;
+        } else {
+            const bool long_rows = k.NM <= 16 && k.B * k.I * k.D >= 10000000 && (k.I % 2 != 0 || k.I >= 16384);
+            if (lt || mfma || k.I <= 64 || long_rows) nts = 0;
+            if (lt && mfma) ntl = 0;
+            if (k.kernel == SJ_LPLUSTIMES) ntl = !nts;
+        }
+    }
     if (k.flags & SJ_FLAG_LOADS_CACHED) ntl = 0;
     if (k.flags & SJ_FLAG_LOADS_NONTEMPORAL) ntl = 1;
     if (k.flags & SJ_FLAG_STORES_CACHED) nts = 0;
@@ -986,8 +1084,12 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
             *name = (k.kernel == SJ_LTIMES) ? "sj_ltimes_staged" : "sj_lplustimes_staged";
         } else if (k.variant == SJ_VAR_MFMA && k.dtype == SJ_F64 && k.I > 1) {
             const bool lt = (k.kernel == SJ_LTIMES);
+            bool wdirect = false;
+            const int64_t split = cols_split(k, &wdirect);
             o << "#define SJ_K " << (lt ? k.D : k.NM) << "\n#define SJ_NOUT " << (lt ? k.NM : k.D) << "\n#define SJ_T "
-              << k.tile_n << "\n#define SJ_PF " << k.unroll << "\n#define SJ_ROTATE " << (k.order == 2 ? 1 : 0) << "\n";
+              << k.tile_n << "\n#define SJ_PF " << k.unroll << "\n#define SJ_ROTATE " << (k.order == 2 ? 1 : 0)
+              << "\n#define SJ_FLAT " << (cols_flat(k) ? 1 : 0) << "\n#define SJ_OS " << split << "\n#define SJ_WDIRECT "
+              << (wdirect ? 1 : 0) << "\n";
             *name = lt ? "sj_ltimes_cols_mfma" : "sj_lplustimes_cols_mfma";
             body = kTpl_cols_mfma64;
         } else if (k.variant == SJ_VAR_MFMA && k.dtype == SJ_F64 && k.kernel == SJ_LTIMES_LPLUS) {

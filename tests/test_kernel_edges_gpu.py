@@ -80,3 +80,35 @@ def test_mass_hex_groups(P, orc, D1D, Q1D, NE):
     assert np.isfinite(got).all()
     assert componentwise_err(got[es].ravel(), orc.mass(3, D1D, Q1D, B1, Ds, Xs),
                              orc.mass(3, D1D, Q1D, B1, Ds, Xs, absolute=True)) <= TOL_F64
+
+
+# the column structures AUTO picks: one partial tile; output blocks shared by two to five waves and a ragged
+# last block; two columns a lane with records shorter than a tile; records crossing tiles with odd lengths; the
+# sizes on both sides of the weights-from-memory line (16,384 columns) and of each structure's line; a tile whose
+# registers send it back to the staged weights
+@pytest.mark.parametrize("layout,Z,G,D,NM,tile", [
+    ("DGZ", 11, 1, 40, 7, {}), ("DZG", 5, 3, 84, 64, {}), ("DGZ", 70, 2, 33, 49, {}), ("ZDG", 31, 6, 130, 16, {}),
+    ("ZDG", 1800, 6, 24, 16, {}), ("GDZ", 41, 7, 57, 25, {}), ("ZDG", 23, 41, 20, 36, {}), ("DGZ", 4096, 4, 48, 16, {}),
+    ("DGZ", 4097, 4, 48, 16, {}), ("ZDG", 8300, 2, 27, 9, {}), ("ZDG", 5500, 3, 16, 4, {}), ("DZG", 13107, 5, 20, 16, {}),
+    ("DZG", 13108, 5, 20, 16, {}), ("DGZ", 65538, 2, 16, 64, {}), ("DGZ", 300, 4, 64, 64, dict(variant=3, unroll=16, block=512)),
+    ("ZDG", 50, 12, 20, 17, dict(variant=3, tile_n=4, unroll=3, order=2))])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_columns(P, orc, layout, Z, G, D, NM, tile, accumulate):
+    from helpers import contraction_inputs
+    L, Lp, psi, phi = contraction_inputs(31, layout, Z, G, D, NM)
+    fl = P.SJ_FLAG_ACCUMULATE if accumulate else 0
+    spec = dict(layout=layout, Z=Z, G=G, D=D, NM=NM, flags=fl, **tile)
+    for k, W, x, n, ref, scale in ((P.SJ_LTIMES, L, psi, NM, orc.ltimes(layout, Z, G, D, NM, L, psi),
+                                    orc.ltimes_absscale(layout, Z, G, D, NM, L, psi)),
+                                   (P.SJ_LPLUSTIMES, Lp, phi, D, orc.lplustimes(layout, Z, G, D, NM, Lp, phi),
+                                    orc.ltimes_absscale(layout, Z, G, NM, D, Lp, phi))):
+        old = np.random.default_rng(n).uniform(-1, 1, n * G * Z) if accumulate else np.full(n * G * Z, np.nan)
+        buf = np.concatenate([old, np.full(64, 7.0)])           # the end of the output is guarded
+        out = dev(buf)
+        h = P.sj_specialize(k, **spec)
+        P.sj_run(h, [dev(W), dev(x), out])
+        got = host(out)
+        assert (got[-64:] == 7.0).all()
+        if accumulate:
+            ref, scale = ref + old, scale + np.abs(old)
+        assert componentwise_err(got[:-64], ref, scale) <= TOL_F64
