@@ -117,7 +117,8 @@ typedef enum sj_variant {
     SJ_VAR_STAGED = 2,   /* rows of contiguous D (or NM) values staged through LDS */
     SJ_VAR_MFMA = 3      /* matrix cores: BF16 dtypes; FP64 row kernel (D innermost) or column kernel;
                             SJ_SCATTERING: FP64 tiles of one moment and 16 zones (the default where
-                            g or z is innermost; with nm innermost, 16-zone blocks staged in LDS) */
+                            g or z is innermost, G <= 32 and the lines are many; with nm innermost,
+                            16-zone blocks staged in LDS); AUTO elsewhere sorts zones by material */
 } sj_variant;
 
 /* Flags. */
@@ -167,7 +168,9 @@ typedef struct sj_spec {
                                per array staged in LDS (256..7168); SJ_SCATTERING, FP64 MFMA with g or
                                z innermost: tiles (one moment, 16 zones) per group of loads (1, 2, 4;
                                nm innermost takes 0 only); 0 = default */
-    int32_t  tile_k;        /* STAGED: reduction values staged per step; 0 = default */
+    int32_t  tile_k;        /* STAGED: reduction values staged per step; SJ_SCATTERING, DIRECT: the zones
+                               per workgroup with which AUTO sorts zones by material, where it does
+                               (as sj_resolve returns it); 0 = default */
     int32_t  unroll;        /* DIRECT: reduction steps whose loads are issued before their FMAs;
                                FP64 MFMA columns: 4-deep reduction steps per group of loads in flight
                                (1..16); BGEMM: 16x16 MFMA tiles per work item (1, 2, 4, 8), each
@@ -181,8 +184,7 @@ typedef struct sj_spec {
                                FP64 MFMA rows (LTimes, LPlusTimes and the fused pair): 1 = each lane
                                reads its operand rows from HBM, 2 = a group's rows move as flat runs
                                through LDS (even D and NM); 0 = 2 where it fits.
-                               SJ_SCATTERING, FP64 MFMA (the default where g or z is innermost and
-                               G <= 32): 1 = tiles taken moments outer (a wave walks along z within a
+                               SJ_SCATTERING, FP64 MFMA: 1 = tiles taken moments outer (a wave walks along z within a
                                moment), 2 = zone blocks outer (the tiles in flight together take the
                                moments of the same zones); 0 = the nesting's outer axis first (2 in
                                ZDG, else 1).

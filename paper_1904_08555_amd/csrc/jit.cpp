@@ -163,6 +163,81 @@ static int64_t cols_split(const SpecKey &k, bool *wdirect)
 // where fewer rows than that are all there is
 static int64_t mlp_tile_rows(int64_t rows) { return rows <= 16 ? 16 : 32; }
 
+// LDS pitches (doubles) of the sorted form with nm innermost: a group's moments (lanes read groups
+// 4 apart: 8 pitches in dwords must not come back to the same of 64 banks), a zone's groups
+static int64_t scattering_sorted_pitch(int64_t NM) { return NM + (NM % 4 == 0 ? 2 : 0); }
+static int64_t scattering_sorted_zone(int64_t G, int64_t NM)
+{
+    const int64_t n = G * scattering_sorted_pitch(NM);
+    return n + (n % 2 == 0 ? 6 : 5);
+}
+
+// Scattering with zones sorted by material: whether SJ_VAR_AUTO takes it, with the zones per block
+// and the threads.  The other structures give a tile of matrix products, or a wave of lines, one
+// material and form the outputs again for each material they meet, so their time depends on how the
+// materials lie; sorted, every product is used once.  Measured on MI355X, us with four to eight
+// materials in zone order / drawn per zone, FP64:
+//   g innermost, G > 32 (before: a thread per line): DZG Z=13824 G=44 NM=9 30/41 against 59/180,
+//     ZDG Z=16310 G=46 NM=25 104/142 against 230/528, Z=20011 G=64 NM=9 73/89 against 170/490.
+//   z innermost, G > 32: a line per thread needs about three waves per SIMD to hide its matrix
+//     reads, so up to 196608 lines (Z=5003 G=40 NM=9 18.7/22 against 22.5/69, Z=2003 G=60 NM=4
+//     9/10.7 against 125/157).  More lines in zone order are faster by the thread (DGZ Z=20011 G=44
+//     NM=16 85/100 against 69/450).
+//   G 17 ... 32 (before: matrix-core tiles of one moment and 16 zones): z innermost, where there are
+//     few waves of tiles (Z=1003 G=32 NM=9 6.7/7.7 against 10.9/34) or, at G = 31 and 32, rows that
+//     are no whole lines (Z=23855 G=32 NM=16 66/77 against 73/188).  Whole lines: 65/80 against
+//     62/230, the tiles; G=24 NM=16 Z=7001 20/24 against 20/34, the tiles.  g innermost: Z=23855
+//     G=32 NM=16 54/66 against 43/101, the tiles.
+//   G <= 16: the tiles, whose 16 zones are as many outputs as one block of 16 has.
+//   nm innermost (rows of G > 1 moments do not lie along 16 zones at all; before: a thread per
+//     line): Z=32768 G=32 NM=16 ZGD 63.8/78 against 62/197 (where the boundaries of the materials
+//     fall between its waves; 120/192 where they do not), GZD Z=30011 68/76 against 120/192;
+//     Z=15077 G=32 NM=9 24/29 against 133, G=55 NM=4 Z=17981 35/88 against 705, Z=33001 G=8 NM=4
+//     8.8/10.1 against 15.5/16; G=4 NM=4 Z=40001 8.3/10.1 against 6.8/7.3: G >= 8.  GZD where a
+//     group's rows lie 64 KiB apart or a multiple of it keeps the thread per line: a block's runs
+//     of all groups fall on the same channels (Z=32768 G=32 NM=16 82/85 against 59/195, though
+//     only if the boundaries fall between waves).
+// Zones per block, nm innermost: two workgroups a CU (one below 16 zones), not so many that a
+// thread's values (20 doubles loaded one by one, or 36 in pairs) and their offsets fill its
+// registers (Z=9000 G=24 NM=25: 36/48 with 8 zones, 52/61 with 16), and a block for every CU
+// (Z=100 G=8 NM=25: 7.7 with 8 zones, 10.4 with 32).
+static bool scattering_sorted_tile(int layout, int64_t Z, int64_t G, int64_t NM, int *zb, int *block)
+{
+    const bool nm_inner = (layout == SJ_GZD || layout == SJ_ZGD) && NM > 1;
+    if (!nm_inner) {
+        const int64_t lines = NM * Z;
+        const bool z_inner = layout == SJ_DGZ || layout == SJ_GDZ;
+        *zb = 64;
+        // (1024 threads have 128 registers each: lines of an odd G, loaded value by value, with 16
+        // fragments would spill)
+        *block = G > 32 ? (G > 48 && G % 2 && !z_inner ? 512 : 1024) : lines > 131072 ? 512 : 256;
+        if (G > 32) return !z_inner || lines <= 196608;
+        return z_inner && ((G >= 31 && (lines <= 131072 || Z % 16 != 0)) || (G > 16 && lines <= 32768));
+    }
+    if (NM > 64 || G < 8 || (layout == SJ_GZD && G <= 32 && Z * NM % 8192 == 0)) return false;
+    const int64_t most = NM % 2 == 0 ? 36 : 20;   // a thread's values
+    *block = G <= 32 ? 256 : 512;
+    for (*zb = 64; *zb > 1 && *zb * scattering_sorted_zone(G, NM) * 8 > (*zb >= 16 ? 76 : 140) * 1024;) *zb /= 2;
+    while (*zb > 8 && *zb * G * NM > most * *block) *zb /= 2;
+    if (*zb * G * NM > most * *block) *block = 512;
+    while (*zb > 4 && (Z + *zb - 1) / *zb < 256) *zb /= 2;
+    return true;
+}
+
+static bool scattering_nm_inner(const SpecKey &k);
+
+static bool scattering_sorted(const SpecKey &k) { return k.kernel == SJ_SCATTERING && k.variant == SJ_VAR_DIRECT && k.tile_k != 0; }
+
+// moments a workgroup of the sorted form takes where nm is not innermost: as many as leave two
+// workgroups a CU (four where a matrix has 16 blocks of 16 x 16)
+static int64_t scattering_sorted_moments(const SpecKey &k)
+{
+    const int64_t blocks = (k.Z + 63) / 64;
+    int64_t mc = k.NM;
+    while (mc > 1 && blocks * ((k.NM + mc - 1) / mc) < (k.G > 48 ? 1024 : 512)) mc = (mc + 1) / 2;
+    return mc;
+}
+
 // Column layouts, every tile field left to the library: whether SJ_VAR_AUTO takes the FP64
 // matrix-core column kernel, and the tile it takes (into *mf).  Measured on MI355X (LTimes / LPlusTimes,
 // us, vector-FMA structure against matrix cores), D = 128 NM = 16 unless said otherwise:
@@ -644,8 +719,8 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
         if (s->G > 64) return fail(SJ_ERR_UNSUPPORTED, "scattering keeps a line's G values in registers: G <= 64");
         if (s->variant != SJ_VAR_AUTO && s->variant != SJ_VAR_DIRECT && s->variant != SJ_VAR_MFMA)
             return fail(SJ_ERR_UNSUPPORTED, "scattering has the DIRECT and MFMA structures");
-        if (s->tile_k != 0 || s->unroll != 0 || s->order < 0 || s->order > 2)
-            return fail(SJ_ERR_INVALID_ARG, "scattering takes tile_n (MFMA only) and order 0, 1 or 2");
+        if ((s->tile_k != 0 && s->variant != SJ_VAR_DIRECT) || s->unroll != 0 || s->order < 0 || s->order > 2)
+            return fail(SJ_ERR_INVALID_ARG, "scattering takes tile_n (MFMA only), tile_k (DIRECT only) and order 0, 1 or 2");
         if (s->flags & SJ_FLAG_ACCUMULATE) return fail(SJ_ERR_INVALID_ARG, "scattering overwrites its output");
         const int64_t lines = s->NM * s->Z;
         if (lines > (int64_t(1) << 40) || s->G * lines > (int64_t(1) << 50)) return fail(SJ_ERR_INVALID_ARG, "array size overflows");
@@ -674,8 +749,16 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
         // after a 1 GiB read that empties the last-level cache: DZG 60.4 us against 135-138 us,
         // ZDG 59.4 us against 148 us, DGZ 64.2 us against 76 us, GDZ 72.5 us against 80 us;
         // materials drawn per zone 142-252 us against 340-358 us)
+        // sorted by material (tile_k, with DIRECT, names the form's zones per block); with nm
+        // innermost all orders are the same lanes
+        int zb = 0, zblock = 0;
+        const bool nm_inner = (s->layout == SJ_GZD || s->layout == SJ_ZGD) && NMv > 1;
+        const bool sorted = scattering_sorted_tile(s->layout, Zv, Gv, NMv, &zb, &zblock) &&
+                            (s->variant == SJ_VAR_AUTO ? s->tile_n == 0 && s->block == 0 && (s->order == 0 || nm_inner)
+                                                       : s->variant == SJ_VAR_DIRECT && s->tile_n == 0 && s->tile_k == zb &&
+                                                             (s->block == 0 || s->block == zblock) && s->order <= 1);
         const bool mfma = (s->variant == SJ_VAR_MFMA) ||
-                          (s->variant == SJ_VAR_AUTO && (sg == 1 || sz == 1) && Gv <= 32);
+                          (s->variant == SJ_VAR_AUTO && !sorted && (sg == 1 || sz == 1) && Gv <= 32);
         if (mfma) {
             // FP64 matrix cores: tiles of one moment and 16 zones, tile_n tiles per group of loads,
             // persistent waves, the fragments of a matrix in registers; g innermost: the tile's
@@ -725,6 +808,19 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
             return (*out = key), SJ_OK;
         }
         if (s->tile_n != 0) return fail(SJ_ERR_INVALID_ARG, "tile_n is the MFMA structure's tiles per group");
+        if (s->tile_k != 0 && !sorted)
+            return fail(SJ_ERR_INVALID_ARG, "scattering DIRECT: tile_k is 0 or the zones per block that AUTO takes");
+        if (sorted) {
+            key.tile_k = zb;
+            key.block = zblock;
+            key.order = 1;
+            key.index64 = (s->G * lines >= (int64_t(1) << 31) || s->count * nl * s->G * s->G >= (int64_t(1) << 31) ||
+                           (s->flags & SJ_FLAG_INDEX64)) ? 1 : 0;
+            const bool xcd = (s->flags & SJ_FLAG_XCD_CONTIGUOUS) != 0;
+            key.flags &= ~(SJ_FLAG_XCD_CONTIGUOUS | SJ_FLAG_XCD_INTERLEAVED);
+            key.flags |= xcd ? SJ_FLAG_XCD_CONTIGUOUS : SJ_FLAG_XCD_INTERLEAVED;
+            return (*out = key), SJ_OK;
+        }
         const bool run_lines = (sg == 1 && std::min(snm, sz) == Gv);
         // lanes along nm only where nm is the faster axis and g is not innermost, or on request
         // (order 2) in ZDG; measured on MI355X at Z=32768 G=32 NM=16 with four materials in zone
@@ -882,6 +978,10 @@ Geometry key_geometry(const SpecKey &k)
         const int64_t groups = (k.NM * ((k.Z + 15) / 16) + k.tile_n - 1) / k.tile_n, waves = k.block / 64;
         g.grid = (unsigned)std::min<int64_t>((groups + waves - 1) / waves, 8192);
         g.persistent = 1;
+    } else if (scattering_sorted(k)) {
+        const int64_t mc = scattering_nm_inner(k) ? k.NM : scattering_sorted_moments(k);
+        g.grid = (unsigned)((k.Z + k.tile_k - 1) / k.tile_k * ((k.NM + mc - 1) / mc));
+        if (scattering_nm_inner(k)) g.persistent = 1;
     } else if (k.kernel == SJ_SCATTERING) {
         g.grid = (unsigned)((k.NM * k.Z + k.block - 1) / k.block);
         if (scattering_pairs(k)) g.grid = (unsigned)((k.NM * ((k.Z + 1) / 2) + k.block - 1) / k.block);
@@ -973,6 +1073,36 @@ static const char *kCommonPrologue =
     "#else\n"
     "#define SJ_STORE(v, p) SJ_STORE_RAW((v), (p))\n"
     "#endif\n";
+
+// Scattering: phi is read once and phi_out written once, so both are streamed (nontemporal), but for the
+// matrix-core forms (us, nontemporal / ordinary, four materials in zone order):
+//   loads, both arrays together within 160 MB, which the last-level cache holds with the producer's or
+//     consumer's use of them: ZDG Z=8001 G=31 NM=25 36/29, DGZ Z=20008 G=30 NM=16 47/33, Z=20016 G=16
+//     17.3/15.6, ZGD Z=20011 G=32 39.6/37.6; beyond it ZDG Z=32768 G=32 55/59;
+//   stores, z innermost, rows that start off a half line: a wave's 128-byte pieces then share lines with
+//     its neighbours' (DGZ Z=50011 G=24 NM=16 178/120, Z=23855 G=32 108/60, Z=150001 G=6 126/76; half lines,
+//     Z=20008, 33/50);
+//   ZDG, lines of less than 128 bytes apart from one another: both (Z=60001 G=5 NM=16 60/33, Z=20011 G=15
+//     31/23), and loads of lines that are no multiple of 128 bytes (Z=50011 G=31 132/120).
+static void scattering_policy(const SpecKey &k, int *nt_load, int *nt_store)
+{
+    int ntl = 1, nts = 1;
+    if (k.variant == SJ_VAR_MFMA || scattering_sorted(k)) {
+        const bool z_inner = k.layout == SJ_DGZ || k.layout == SJ_GDZ;
+        if (16 * k.NM * k.G * k.Z <= 160000000) ntl = 0;
+        if (k.variant == SJ_VAR_MFMA) {
+            if (z_inner && k.Z % 8 != 0) nts = 0;
+            if (k.layout == SJ_ZDG && k.G % 16 != 0) ntl = 0;
+            if (k.layout == SJ_ZDG && k.G < 16) nts = 0;
+        }
+    }
+    if (k.flags & SJ_FLAG_LOADS_CACHED) ntl = 0;
+    if (k.flags & SJ_FLAG_LOADS_NONTEMPORAL) ntl = 1;
+    if (k.flags & SJ_FLAG_STORES_CACHED) nts = 0;
+    if (k.flags & SJ_FLAG_STORES_NONTEMPORAL) nts = 1;
+    *nt_load = ntl;
+    *nt_store = nts;
+}
 
 void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
 {
@@ -1144,8 +1274,7 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
         static const char *lay[6] = {"dgz", "dzg", "gdz", "gzd", "zdg", "zgd"};
         if (k.variant == SJ_VAR_MFMA) {
             int ntl = 1, nts = 1;
-            if (k.flags & SJ_FLAG_LOADS_CACHED) ntl = 0;
-            if (k.flags & SJ_FLAG_STORES_CACHED) nts = 0;
+            scattering_policy(k, &ntl, &nts);
             o << "#define SJ_NM " << NM << "\n#define SJ_G " << G << "\n#define SJ_Z " << Z << sfx << "\n#define SJ_NMAT "
               << k.rows << "\n#define SJ_NL " << nl << "\n#define SJ_SNM " << snm << sfx << "\n#define SJ_SZ " << sz << sfx
               << "\n#define SJ_SG " << sg << sfx << "\n#define SJ_RT " << k.tile_n << "\n#define SJ_ZMAJOR " << (k.order == 2 ? 1 : 0)
@@ -1159,9 +1288,8 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
         } else {
         o << "#define SJ_PERSIST " << (scattering_persistent(k) ? 1 : 0) << "\n#define SJ_PAIR "
           << (scattering_pairs(k) ? 1 : 0) << "\n";
-        int ntl = 1, nts = 1;   // phi is read once and phi_out written once: streamed
-        if (k.flags & SJ_FLAG_LOADS_CACHED) ntl = 0;
-        if (k.flags & SJ_FLAG_STORES_CACHED) nts = 0;
+        int ntl = 1, nts = 1;
+        scattering_policy(k, &ntl, &nts);
         o << "#define SJ_NM " << NM << "\n#define SJ_G " << G << "\n#define SJ_Z " << Z << sfx << "\n#define SJ_NMAT "
           << k.rows << "\n#define SJ_NL " << nl << "\n#define SJ_SNM " << snm << sfx << "\n#define SJ_SG " << sg << sfx
           << "\n#define SJ_SZ " << sz << sfx << "\n#define SJ_LANE_NM " << (lane_nm ? 1 : 0) << "\n#define SJ_RUN_LINES "
@@ -1170,6 +1298,20 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
           << k.block << "\n#define SJ_NT_LOAD " << ntl << "\n#define SJ_NT_STORE " << nts << "\n#define SJ_ACCUM 0\n"
           << "#define SJ_XCD " << ((k.flags & SJ_FLAG_XCD_CONTIGUOUS) ? 8 : 0) << "\n" << kXcdHelper;
         body = kTpl_scattering_direct;
+        if (scattering_sorted(k)) {
+            if (scattering_nm_inner(k)) {
+                int64_t per_zone = 0;   // tiles of a zone whose material it has to itself: the most there can be
+                for (int64_t d = 0; d < nl; ++d) per_zone += (std::min(2 * d + 1, NM - d * d) + 15) / 16;
+                o << "#define SJ_ZB " << k.tile_k << "\n#define SJ_NP " << scattering_sorted_pitch(NM) << "\n#define SJ_ZP "
+                  << scattering_sorted_zone(G, NM)
+                  << "\n#define SJ_MAXT " << k.tile_k * per_zone << "\n#define SJ_ZOUTER " << (sz > sg ? 1 : 0)
+                  << "\n#define SJ_OBW " << (G <= 32 ? (G + 15) / 16 : 1) << "\n";
+                body = kTpl_scattering_rows_sorted;
+            } else {
+                o << "#define SJ_MC " << scattering_sorted_moments(k) << "\n#define SJ_SLOTS " << (k.block == 256 && G <= 28 ? 2 : 1) << "\n";
+                body = kTpl_scattering_zones;
+            }
+        }
         *name = std::string("sj_scattering_direct_") + lay[k.layout];
         o << "#define SJ_KERNEL_NAME " << *name << "\n";
         }

@@ -112,3 +112,43 @@ def test_columns(P, orc, layout, Z, G, D, NM, tile, accumulate):
         if accumulate:
             ref, scale = ref + old, scale + np.abs(old)
         assert componentwise_err(got[:-64], ref, scale) <= TOL_F64
+
+
+# zones sorted by material: one zone, a full block and its neighbours, a material for every zone;
+# the group counts around 16-wide blocks; cut-off degrees, odd and even runs of moments; the larger
+# blocks of lines (nm not innermost)
+@pytest.mark.parametrize("layout,Z,G,NM,nmat", [
+    ("DGZ", 1, 17, 1, 1), ("GDZ", 63, 32, 5, 3), ("DGZ", 129, 28, 9, 200), ("GDZ", 8201, 31, 17, 5), ("DZG", 8200, 33, 17, 5),
+    ("DZG", 64, 33, 4, 1), ("ZDG", 65, 48, 10, 70), ("DGZ", 130, 49, 3, 4), ("ZDG", 77, 64, 16, 2), ("GDZ", 1, 64, 2, 3),
+    ("ZGD", 1, 8, 2, 1), ("GZD", 65, 9, 3, 3), ("ZGD", 1030, 16, 7, 4), ("GZD", 100, 32, 9, 150), ("ZGD", 4100, 32, 16, 4),
+    ("GZD", 20, 24, 25, 6), ("ZGD", 33, 33, 50, 5), ("GZD", 33, 55, 4, 7), ("ZGD", 17, 64, 64, 2), ("GZD", 9, 32, 64, 9)])
+def test_scattering_sorted(P, orc, layout, Z, G, NM, nmat):
+    import math
+    import sj_inputs as gen
+    rng = np.random.default_rng(Z + G)
+    nl = math.isqrt(NM - 1) + 1
+    S = rng.uniform(-1, 1, (nmat, nl, G, G))
+    phi = gen.to_layout(rng.uniform(-1, 1, (NM, G, Z)), layout).ravel()
+    spec = dict(layout=layout, Z=Z, G=G, NM=NM, count=nmat)
+    r = P.sj_resolve(P.SJ_SCATTERING, **spec)
+    assert r["tile_k"] > 0
+    h = P.sj_specialize(P.SJ_SCATTERING, **spec)
+    assert P.sj_specialize(P.SJ_SCATTERING, **spec, variant=P.SJ_VAR_DIRECT, tile_k=r["tile_k"]) == h
+    for bad in (dict(tile_k=r["tile_k"] + 1), dict(tile_k=r["tile_k"], block=64), dict(tile_k=r["tile_k"], tile_n=1)):
+        with pytest.raises(P.SJError):
+            P.sj_specialize(P.SJ_SCATTERING, **spec, variant=P.SJ_VAR_DIRECT, **bad)
+    for mat in (rng.integers(0, nmat, Z), np.arange(Z) % nmat, np.arange(Z) * nmat // Z, np.full(Z, nmat - 1)):
+        mat = mat.astype(np.int32)
+        ref = orc.scattering(layout, Z, G, NM, S, mat, phi)
+        scale = orc.scattering(layout, Z, G, NM, np.abs(S), mat, np.abs(phi))
+        out = dev(np.concatenate([np.full(NM * G * Z, np.nan), np.full(64, 7.0)]))   # the end is guarded
+        P.sj_run(h, [dev(S.ravel()), dev(mat), dev(phi), out])
+        got = host(out)
+        assert (got[-64:] == 7.0).all()
+        assert componentwise_err(got[:-64], ref, scale) <= TOL_F64
+    mat[rng.integers(0, Z)] = -1
+    mat[0] = nmat                                           # no such material: NaN, and only there
+    P.sj_run(h, [dev(S.ravel()), dev(mat), dev(phi), out])
+    after = host(out)[:-64]
+    bad = gen.to_layout(np.broadcast_to((mat < 0) | (mat >= nmat), (NM, G, Z)).copy(), layout).ravel()
+    assert np.isnan(after[bad]).all() and (after[~bad] == got[:-64][~bad]).all()
