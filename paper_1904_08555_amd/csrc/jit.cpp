@@ -294,6 +294,32 @@ static int64_t scattering_block_lds(int64_t NM, int64_t G)
     return 16 * (G * nmp + 2) * 8;
 }
 
+// Fused columns on the matrix cores: columns per lane and threads, and whether SJ_VAR_AUTO takes the form.
+// A thread per column takes about as long for a few columns as for 100,000, one walk over the
+// directions; the matrix-core form's time follows the columns.  Measured on MI355X (us, thread
+// per column / matrix cores):
+//   columns        24000      45000       64000      90000      130000
+//   D=96 NM=4     15.5/7.2   18.8/17.6   22.6/23.7  25.3/29.6  33.2/41.3
+//   D=96 NM=16    29.7/11.9  30.2/21.4   31.4/27.5  34.5/34.9  43.1/49.9
+//   D=56 NM=16    18.5/6.4   18.9/13.4   19.5/16.8  19.9/20.9  21.6/28.9
+//   D=96 NM=36    60.4/14.5  60.4/29.7   60.7/39.3  61.2/51.9  64.8/69.6
+//   D=96 NM=64    83/25      83/46       84/59      85/79      90/110
+// and with an odd column extent, one column per lane, Z=8001 G=5 NM=16 22.0/21.4, 90,000 columns,
+// NM = 36 62/86.  Two columns per lane from 8192 columns on (a workgroup a CU; 3768 columns
+// D=120 NM=64 10.8 with two, 8.9 with one; 13960 D=104 NM=25 10.9 and 13.2).  512 threads are
+// slower everywhere (D=88 NM=64, 15240 columns 20.0 against 16.2).
+static bool fused_cols_tile(int64_t B, int64_t I, int64_t NM, int *tile, int *block)
+{
+    const int64_t cols = B * I;
+    *tile = I % 2 == 0 && NM <= 64 && cols >= 8192 ? 2 : 1;   // (NM * 2 within the thread per column's limit, 128)
+    *block = 256;
+    if (I == 1 || NM > 128) return false;
+    if (I % 2 != 0 || NM > 64) return cols <= (NM < 25 ? 32768 : 49152);
+    return cols <= (NM < 9 ? 49152 : NM < 17 ? 65536 : 90112);
+}
+
+static bool fused_cols(const SpecKey &k) { return k.kernel == SJ_LTIMES_LPLUS && k.variant == SJ_VAR_DIRECT && k.tile_k != 0; }
+
 sj_status make_key(sj_kernel k, const sj_spec *s, int device, const char *arch, SpecKey *out)
 {
     if (!s || !out) return fail(SJ_ERR_INVALID_ARG, "null spec or output");
@@ -323,6 +349,10 @@ sj_status make_key(sj_kernel k, const sj_spec *s, int device, const char *arch, 
     for (int i = 0; i < n; ++i) {
         sj_spec t = *s;
         t.variant = order[i];
+        int ct = 0, cblock = 0;
+        if (k == SJ_LTIMES_LPLUS && t.variant == SJ_VAR_DIRECT && t.tile_n == 0 && t.unroll == 0 && t.block == 0 && t.order == 0 &&
+            fused_cols_tile(B, I, t.NM, &ct, &cblock))
+            t.tile_k = 16 * ct;
         st = make_key_one(k, &t, device, arch, out);
         if (st != SJ_ERR_UNSUPPORTED) return st;
     }
@@ -450,12 +480,22 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
             // NM = 25: 317 us against 195 us rolled; D = 48, NM = 9, under the line, 81 us either way).
             key.full_unroll = (red * outn * vec * (k == SJ_LTIMES_LPLUS ? 2 : 1) <= 1024) ? 1 : 0;
             key.tile_k = 0;
+            int ct = 0, cblock = 0;
+            if (k == SJ_LTIMES_LPLUS && fused_cols_tile(key.B, key.I, s->NM, &ct, &cblock) &&
+                s->unroll == 0 && s->order <= 1 && (s->tile_n == 0 || s->tile_n == ct) && (s->block == 0 || s->block == cblock) &&
+                s->tile_k == 16 * ct) {
+                key.tile_n = ct;
+                key.tile_k = 16 * ct;
+                key.block = cblock;
+                key.unroll = 0;
+                key.full_unroll = 0;
+            }
             // Rotation pays when consecutive rows are >= 1 MiB apart (measured on MI355X:
             // 8 MiB row stride, 5.35 TB/s ascending vs 6.2 TB/s rotated).
             int order = s->order;
             if (order == 0) order = (key.I * 8 >= (int64_t(1) << 20)) ? 2 : 1;
             if (order != 1 && order != 2) return fail(SJ_ERR_INVALID_ARG, "order must be 0, 1 or 2");
-            if ((k == SJ_LTIMES ? s->D : s->D) < 2 * key.unroll) order = 1;  // fewer than two row groups
+            if ((k == SJ_LTIMES ? s->D : s->D) < 2 * key.unroll || key.tile_k != 0) order = 1;  // fewer than two row groups
             key.order = order;
         } else if (var == SJ_VAR_STAGED) {
             if (s->order != 0 && s->order != 1) return fail(SJ_ERR_INVALID_ARG, "this structure has no order 2");
@@ -1004,7 +1044,9 @@ Geometry key_geometry(const SpecKey &k)
         }
     }
     if (k.kernel == SJ_LTIMES || k.kernel == SJ_LPLUSTIMES || k.kernel == SJ_LTIMES_LPLUS) {
-        if (k.variant == SJ_VAR_DIRECT) {
+        if (fused_cols(k)) {
+            g.grid = (unsigned)((k.B * k.I + k.tile_k - 1) / k.tile_k);
+        } else if (k.variant == SJ_VAR_DIRECT) {
             const int64_t nv = k.B * (k.I / k.tile_n);
             g.grid = (unsigned)((nv + k.block - 1) / k.block);
         } else if (k.variant == SJ_VAR_STAGED) {
@@ -1134,7 +1176,13 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
     // 18.6 nontemporal, 24.8 ordinary), forms them from many moments (GDZ rows of 30,010, D = 96, NM = 25
     // 158 / 198) or in 16-byte pieces of middling rows (GDZ rows of 6,330, D = 80, NM = 16 97 / 109; of
     // 30,882, D = 112 231 / 217).  The matrix-core form reads ragged rows in 128-byte pieces: ordinary loads.
-    if (k.dtype == SJ_F64 && k.I > 1 && (ntl || nts)) {
+    // The fused matrix-core columns are few enough to stay in the caches: ordinary loads (DZG 25,485 columns,
+    // D = 82, NM = 25 19.9 nontemporal, 14.5 ordinary; ZDG 1017 x 42, NM = 16 19.2 / 14.3), and stores where short
+    // rows share lines (GDZ rows of 66, NM = 25 5.3 / 4.8).
+    if (fused_cols(k)) {
+        ntl = 0;
+        nts = k.I % 16 == 0 || k.I > 256;
+    } else if (k.dtype == SJ_F64 && k.I > 1 && (ntl || nts)) {
         const bool ragged = k.I % 16 != 0, mfma = k.variant == SJ_VAR_MFMA, lt = k.kernel == SJ_LTIMES;
         const bool big = 8 * k.B * k.I * (k.D + k.NM) > (int64_t(32) << 20);
         if (!ragged) {
@@ -1187,7 +1235,11 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
         o << "#define SJ_NT_LOAD " << ntl << "\n#define SJ_NT_STORE " << nts << "\n#define SJ_ACCUM "
           << ((k.flags & SJ_FLAG_ACCUMULATE) ? 1 : 0) << "\n#define SJ_XCD " << (xcd_contiguous(k) ? 8 : 0) << "\n"
           << kXcdHelper;
-        if (k.variant == SJ_VAR_DIRECT) {
+        if (fused_cols(k)) {
+            o << "#define SJ_T " << k.tile_n << "\n";
+            body = kTpl_fused_cols_mfma64;
+            *name = "sj_ltimes_lplus_direct";
+        } else if (k.variant == SJ_VAR_DIRECT) {
             o << "#define SJ_VEC " << k.tile_n << "\n#define SJ_UNROLL " << k.unroll << "\n#define SJ_FULL_UNROLL "
               << k.full_unroll << "\n#define SJ_ROTATE " << (k.order == 2 ? 1 : 0) << "\n";
             if (k.kernel == SJ_LTIMES_LPLUS) {

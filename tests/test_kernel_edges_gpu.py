@@ -152,3 +152,33 @@ def test_scattering_sorted(P, orc, layout, Z, G, NM, nmat):
     after = host(out)[:-64]
     bad = gen.to_layout(np.broadcast_to((mat < 0) | (mat >= nmat), (NM, G, Z)).copy(), layout).ravel()
     assert np.isnan(after[bad]).all() and (after[~bad] == got[:-64][~bad]).all()
+
+
+# fused contractions on the matrix cores: one column, one and two columns per lane, columns that end
+# inside a tile or cross rows, directions fewer than the waves' steps, around 16-wide blocks and beyond
+# the loads in flight, the most moments
+@pytest.mark.parametrize("layout,Z,G,D,NM", [
+    ("DGZ", 2, 1, 1, 1), ("GDZ", 17, 3, 5, 4), ("ZDG", 5, 3, 17, 15), ("DZG", 33, 2, 15, 17), ("ZDG", 400, 22, 31, 16),
+    ("DGZ", 4099, 2, 33, 33), ("GDZ", 8193, 1, 130, 9), ("DZG", 1200, 11, 129, 25), ("DGZ", 100, 1, 64, 128), ("GDZ", 4098, 3, 65, 113),
+    ("ZDG", 2049, 4, 144, 48)])
+def test_fused_columns(P, orc, layout, Z, G, D, NM):
+    from helpers import contraction_inputs
+    L, Lp, psi, _ = contraction_inputs(47, layout, Z, G, D, NM)
+    spec = dict(layout=layout, Z=Z, G=G, D=D, NM=NM)
+    r = P.sj_resolve(P.SJ_LTIMES_LPLUS, **spec)
+    assert r["tile_k"] == 16 * r["tile_n"] > 0
+    h = P.sj_specialize(P.SJ_LTIMES_LPLUS, **spec)
+    assert P.sj_specialize(P.SJ_LTIMES_LPLUS, **spec, variant=P.SJ_VAR_DIRECT, tile_n=r["tile_n"], tile_k=r["tile_k"],
+                           block=r["block"], order=r["order"]) == h
+    ref_phi = orc.ltimes(layout, Z, G, D, NM, L, psi)
+    s_phi = orc.ltimes_absscale(layout, Z, G, D, NM, L, psi)
+    ref = orc.lplustimes(layout, Z, G, D, NM, Lp, ref_phi)
+    scale = orc.ltimes_absscale(layout, Z, G, NM, D, Lp, s_phi)
+    for want_phi in (True, False):
+        out = dev(np.concatenate([np.full(D * G * Z, np.nan), np.full(64, 7.0)]))     # the ends are guarded
+        phi = dev(np.concatenate([np.full(NM * G * Z, np.nan), np.full(64, 7.0)]))
+        P.sj_run(h, [dev(L), dev(Lp), dev(psi), out] + ([phi] if want_phi else []))
+        got, gphi = host(out), host(phi)
+        assert (got[-64:] == 7.0).all() and (gphi[-64:] == 7.0).all()
+        assert componentwise_err(got[:-64], ref, scale) <= TOL_F64
+        assert np.isnan(gphi[:-64]).all() if not want_phi else componentwise_err(gphi[:-64], ref_phi, s_phi) <= TOL_F64
