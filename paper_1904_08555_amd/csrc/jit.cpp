@@ -245,13 +245,15 @@ static int64_t scattering_sorted_moments(const SpecKey &k)
 //   14 / 16; 131,072: 34 / 32 against 29 / 30; 524,288: 106 / 109 against 122 / 107.
 // One thread per column or two leaves the chip idle below that and each thread a chain of D NM FMAs fed
 // by scalar loads; a wave per 16 columns does not.  With many columns the vector form is at the memory
-// rate, except for high orders (NM = 64, 2M columns: 820 / 905 against 738 / 742).  Rows that are no
+// rate, except for high orders (NM = 64, 2M columns: 820 / 905 against 738 / 742; LTimes where the moments fill
+// their blocks of 16: NM = 49, DZG 640,000 columns, D = 88 168 / 181 against 199 / 189, ZDG 20000 x 32
+// 158 / 332 against 192 / 173).  Rows that are no
 // multiple of a 128-byte line move the line down (65,535 columns 25 / 18 against 20 / 18), few moments too
 // (NM = 4, D = 48, 65,536 columns: 6.5 / 5.9 against 6.6 / 5.9).  Very short rows (ZDG with up to 8 groups)
 // take the matrix cores at any size: a quarter-wave covers 16 columns whatever record they are in
 // (62,035 zones of 2 groups, D = 27, NM = 9: 12 / 14 against 8.4 / 9.6).  Chains of up to 256 products
 // are done within a launch's time either way.
-static bool cols_mfma_tile(const sj_spec *s, int64_t B, int64_t I, sj_spec *mf)
+static bool cols_mfma_tile(const sj_spec *s, bool ltimes, int64_t B, int64_t I, sj_spec *mf)
 {
     if (I <= 1 || s->tile_n || s->tile_k || s->unroll || s->block || s->order) return false;
     if (s->D < 1 || s->NM < 1 || s->D > 4096 || s->NM > 4096 || I > (int64_t(1) << 50) / B) return false;
@@ -260,7 +262,8 @@ static bool cols_mfma_tile(const sj_spec *s, int64_t B, int64_t I, sj_spec *mf)
     if (!short_rows) {
         if (s->D * s->NM <= 256) return false;
         const int64_t most = (ragged ? 65536 : 131072) / (s->NM < 9 ? 2 : 1);
-        if (cols > most && !(s->NM > 48 && !ragged)) return false;
+        const bool high = s->NM > 48 && (!ltimes || 20 * ((s->NM + 15) / 16 * 16) <= 23 * s->NM);
+        if (cols > most && !(high && !ragged)) return false;
     }
     mf->variant = SJ_VAR_MFMA;
     mf->unroll = 8;
@@ -335,7 +338,7 @@ sj_status make_key(sj_kernel k, const sj_spec *s, int device, const char *arch, 
     static const int kFusedRows[2] = {SJ_VAR_MFMA, SJ_VAR_DIRECT};
     static const int kFusedCols[1] = {SJ_VAR_DIRECT};
     sj_spec mf = *s;
-    if (k != SJ_LTIMES_LPLUS && cols_mfma_tile(s, B, I, &mf)) {
+    if (k != SJ_LTIMES_LPLUS && cols_mfma_tile(s, k == SJ_LTIMES, B, I, &mf)) {
         const sj_status st = make_key_one(k, &mf, device, arch, out);
         if (st != SJ_ERR_UNSUPPORTED) return st;
     }
@@ -1165,17 +1168,20 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
     int ntl = ((k.kernel == SJ_LTIMES || k.kernel == SJ_LTIMES_LPLUS) && streamed && !direct_rows && !bf16_rows) ? 1 : 0;
     int nts = (streamed && !bf16_rows) ? 1 : 0;
     // FP64 columns.  LTimes stores the moments that LPlusTimes reads next: ordinary stores keep them in
-    // the last-level cache, from where LPlusTimes takes them with nontemporal loads (pairs, us, nontemporal
-    // stores and ordinary loads against these: DGZ 32768 x 32, D = 96, NM = 16 347 / 320; 20000 x 32, NM = 36
-    // 296 / 257; DZG 64000 x 32, D = 128, NM = 64 1432 / 1389); arrays of up to 32 MB stay in the caches
-    // either way (29 MB: 9.6 / 9.5).
+    // the last-level cache (pairs, us, nontemporal
+    // stores and ordinary loads against these: DZG 20000 x 32, D = 104, NM = 25 277 / 238; D = 64, NM = 36
+    // 236 / 179; DGZ 20000 x 32, NM = 36 296 / 257).  From NM = 49 on LPlusTimes takes them with nontemporal
+    // loads (DZG 20000 x 32, D = 56, NM = 64 325 / 267, 302 with ordinary loads; at D = 104, NM = 25 238 with
+    // ordinary, 248 with nontemporal loads, and by itself 118 and 143).  Arrays of up to 32 MB stay in the
+    // caches either way (29 MB: 9.6 / 9.5).
     // Rows that are no multiple of a 128-byte line: pieces that share a line come from different
     // instructions or waves, so ordinary stores (ZDG 16,312 zones of 41 groups, D = 120, NM = 36 540 / 490;
     // GDZ rows of 8,671, D = 112, NM = 4 40.5 / 33.3; matrix cores, ZDG 1,387 x 47, D = 72, NM = 16 43 / 25),
     // but not where LPlusTimes writes longer rows that the caches hold (DGZ 46,341 columns, D = 112, NM = 4
     // 18.6 nontemporal, 24.8 ordinary), forms them from many moments (GDZ rows of 30,010, D = 96, NM = 25
     // 158 / 198) or in 16-byte pieces of middling rows (GDZ rows of 6,330, D = 80, NM = 16 97 / 109; of
-    // 30,882, D = 112 231 / 217).  The matrix-core form reads ragged rows in 128-byte pieces: ordinary loads.
+    // 30,882, D = 112 231 / 217) or, fused, after many moments (ZDG 4,100 x 30, D = 64, NM = 36 47 / 84; D = 96,
+    // NM = 16 54 / 50).  The matrix-core form reads ragged rows in 128-byte pieces: ordinary loads.
     // The fused matrix-core columns are few enough to stay in the caches: ordinary loads (DZG 25,485 columns,
     // D = 82, NM = 25 19.9 nontemporal, 14.5 ordinary; ZDG 1017 x 42, NM = 16 19.2 / 14.3), and stores where short
     // rows share lines (GDZ rows of 66, NM = 25 5.3 / 4.8).
@@ -1187,10 +1193,10 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
         const bool big = 8 * k.B * k.I * (k.D + k.NM) > (int64_t(32) << 20);
         if (!ragged) {
             if (lt && big) nts = 0;
-            if (k.kernel == SJ_LPLUSTIMES && big) ntl = 1;
+            if (k.kernel == SJ_LPLUSTIMES && big && k.NM > 48) ntl = 1;
         } else {
             const bool long_rows = k.NM <= 16 && k.B * k.I * k.D >= 10000000 && (k.I % 2 != 0 || k.I >= 16384);
-            if (lt || mfma || k.I <= 64 || long_rows) nts = 0;
+            if (lt || mfma || (k.I <= 64 && (k.kernel == SJ_LPLUSTIMES || k.NM <= 16)) || long_rows) nts = 0;
             if (lt && mfma) ntl = 0;
             if (k.kernel == SJ_LPLUSTIMES) ntl = !nts;
         }
