@@ -171,8 +171,9 @@ typedef struct sj_spec {
     int32_t  tile_k;        /* STAGED: reduction values staged per step; SJ_SCATTERING, DIRECT: the zones
                                per workgroup with which AUTO sorts zones by material, where it does;
                                fused, DIRECT, column layouts: the columns per workgroup of AUTO's
-                               matrix-core form, where it takes it (both as sj_resolve returns
-                               them); 0 = default */
+                               matrix-core form, where it takes it; MFMA, D innermost, few rows:
+                               4 = AUTO's column form (all as sj_resolve returns them);
+                               0 = default */
     int32_t  unroll;        /* DIRECT: reduction steps whose loads are issued before their FMAs;
                                FP64 MFMA columns: 4-deep reduction steps per group of loads in flight
                                (1..16); BGEMM: 16x16 MFMA tiles per work item (1, 2, 4, 8), each

@@ -133,6 +133,13 @@ static void layout_view(int layout, int64_t Z, int64_t G, int64_t *B, int64_t *I
 
 static bool cols_flat(const SpecKey &k) { return k.B > 1 && k.I % (16 * k.tile_n) != 0; }
 
+// the column kernel: a column axis innermost, or few rows of D (or NM) values as columns one apart
+static bool cols_mfma(const SpecKey &k)
+{
+    return k.variant == SJ_VAR_MFMA && k.dtype == SJ_F64 && (k.kernel == SJ_LTIMES || k.kernel == SJ_LPLUSTIMES) &&
+           (k.I > 1 || k.tile_k == 4);
+}
+
 static int64_t cols_tiles(const SpecKey &k)
 {
     const int64_t cols = 16 * k.tile_n;
@@ -280,6 +287,19 @@ static bool cols_mfma_tile(const sj_spec *s, bool ltimes, int64_t B, int64_t I, 
     return true;
 }
 
+// Few rows (D innermost) as columns one value apart: whether AUTO takes the column kernel, a wave per
+// 16 rows and some of the 16-output blocks with the weights straight from memory (cols_split), for them.
+// The row kernels build the weight fragments and a chain over all outputs in each of a few waves.
+// Measured on MI355X (LTimes / LPlusTimes, us, row kernels against this): D = 96, NM = 36 64 rows 10.3 / 9.9
+// against 4.2 / 2.9, 3,001 11.3 / 11.3 against 6.4 / 4.1, 12,000 12.6 / 11.4 against 11.4 / 8.6; D = 96,
+// NM = 16 1,501 rows 6.0 / 3.7 against 4.2 / 3.2, 6,000 6.1 / 4.0 against 5.3 / 4.6; D = 120, NM = 64 3,001 rows
+// 11.3 / 12.0 against 6.3 / 6.7, 12,000 12.8 / 12.9 against 15.4 / 18.5; D = 56, NM = 9 6,000 rows 4.8 / 4.5
+// against 3.1 / 3.2; D = 113, NM = 16 6,000 rows 8.7 / 9.3 against 5.6 / 5.3.
+static bool rows_as_cols(int64_t rows, int64_t NM)
+{
+    return rows <= ((NM > 9 && NM <= 16) || NM > 36 ? 4096 : 8192);
+}
+
 static bool valid_block(int b) { return b >= 64 && b <= 1024 && b % 64 == 0; }
 
 static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const char *arch, SpecKey *out);
@@ -339,6 +359,17 @@ sj_status make_key(sj_kernel k, const sj_spec *s, int device, const char *arch, 
     static const int kFusedCols[1] = {SJ_VAR_DIRECT};
     sj_spec mf = *s;
     if (k != SJ_LTIMES_LPLUS && cols_mfma_tile(s, k == SJ_LTIMES, B, I, &mf)) {
+        const sj_status st = make_key_one(k, &mf, device, arch, out);
+        if (st != SJ_ERR_UNSUPPORTED) return st;
+    }
+    if (k != SJ_LTIMES_LPLUS && I == 1 && !s->tile_n && !s->tile_k && !s->unroll && !s->block && !s->order && s->D >= 1 &&
+        s->NM >= 1 && s->D <= 4096 && s->NM <= 4096 && rows_as_cols(B, s->NM)) {
+        mf.variant = SJ_VAR_MFMA;
+        mf.tile_n = 1;
+        mf.tile_k = 4;
+        mf.unroll = (int32_t)std::min<int64_t>(8, ((k == SJ_LTIMES ? s->D : s->NM) + 3) / 4);
+        mf.block = 64;
+        mf.order = 1;
         const sj_status st = make_key_one(k, &mf, device, arch, out);
         if (st != SJ_ERR_UNSUPPORTED) return st;
     }
@@ -564,7 +595,9 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
             key.unroll = 0;
             key.tile_k = 16;
             key.full_unroll = 1;
-        } else if (s->dtype == SJ_F64 && key.I > 1) {
+        } else if (s->dtype == SJ_F64 &&
+                   (key.I > 1 || (s->tile_k == 4 && rows_as_cols(key.B, s->NM) && s->tile_n == 1 &&
+                                  s->unroll == std::min<int64_t>(8, (red + 3) / 4) && s->block == 64 && s->order == 1))) {
             // FP64 matrix-core column contraction: tile_n = columns per lane (1, 2, 4),
             // unroll = 4-deep reduction steps per group of loads in flight, order 2 = rotated groups.
             key.block = s->block ? s->block : 256;
@@ -1054,7 +1087,7 @@ Geometry key_geometry(const SpecKey &k)
             g.grid = (unsigned)((nv + k.block - 1) / k.block);
         } else if (k.variant == SJ_VAR_STAGED) {
             g.grid = (unsigned)((k.B + k.tile_n - 1) / k.tile_n);
-        } else if (k.variant == SJ_VAR_MFMA && k.dtype == SJ_F64 && k.I > 1) {
+        } else if (cols_mfma(k)) {
             bool wdirect = false;
             const int64_t items = cols_tiles(k) * cols_split(k, &wdirect), waves = k.block / 64;
             g.grid = (unsigned)std::min<int64_t>((items + waves - 1) / waves, 2048);
@@ -1185,7 +1218,9 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
     // The fused matrix-core columns are few enough to stay in the caches: ordinary loads (DZG 25,485 columns,
     // D = 82, NM = 25 19.9 nontemporal, 14.5 ordinary; ZDG 1017 x 42, NM = 16 19.2 / 14.3), and stores where short
     // rows share lines (GDZ rows of 66, NM = 25 5.3 / 4.8).
-    if (fused_cols(k)) {
+    if (cols_mfma(k) && k.I == 1) {
+        ntl = nts = 0;   // lines are read and written in pieces of 32 bytes
+    } else if (fused_cols(k)) {
         ntl = 0;
         nts = k.I % 16 == 0 || k.I > 256;
     } else if (k.dtype == SJ_F64 && k.I > 1 && (ntl || nts)) {
@@ -1270,7 +1305,7 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
             o << "#define SJ_TILE_N " << k.tile_n << "\n#define SJ_TILE_K " << k.tile_k << "\n";
             body = (k.kernel == SJ_LTIMES) ? kTpl_ltimes_staged : kTpl_lplustimes_staged;
             *name = (k.kernel == SJ_LTIMES) ? "sj_ltimes_staged" : "sj_lplustimes_staged";
-        } else if (k.variant == SJ_VAR_MFMA && k.dtype == SJ_F64 && k.I > 1) {
+        } else if (cols_mfma(k)) {
             const bool lt = (k.kernel == SJ_LTIMES);
             bool wdirect = false;
             const int64_t split = cols_split(k, &wdirect);

@@ -182,3 +182,20 @@ def test_fused_columns(P, orc, layout, Z, G, D, NM):
         assert (got[-64:] == 7.0).all() and (gphi[-64:] == 7.0).all()
         assert componentwise_err(got[:-64], ref, scale) <= TOL_F64
         assert np.isnan(gphi[:-64]).all() if not want_phi else componentwise_err(gphi[:-64], ref_phi, s_phi) <= TOL_F64
+
+
+# few rows as columns: one row, a tile and its neighbours, ragged outputs and reductions, the last
+# row count of the rule
+@pytest.mark.parametrize("layout,Z,G,D,NM", [
+    ("ZGD", 1, 1, 1, 1), ("GZD", 15, 1, 5, 17), ("ZGD", 17, 3, 33, 16), ("GZD", 16, 4, 96, 25), ("ZDG", 130, 1, 113, 36),
+    ("ZGD", 33, 31, 120, 64), ("GZD", 64, 64, 48, 49), ("ZGD", 8192, 1, 31, 9)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_few_rows(P, orc, layout, Z, G, D, NM, accumulate):
+    for k in (P.SJ_LTIMES, P.SJ_LPLUSTIMES):
+        spec = dict(layout=layout, Z=Z, G=G, D=D, NM=NM)
+        h = P.sj_specialize(k, **spec)
+        assert "cols_mfma" in P.sj_handle_info(h)["kernel_name"]
+        r = P.sj_resolve(k, **spec)
+        assert P.sj_specialize(k, **{f: r[f] for f in ("layout", "Z", "G", "D", "NM", "variant", "tile_n", "tile_k", "unroll",
+                                                       "block", "order", "flags")}) == h
+    test_columns(P, orc, layout, Z, G, D, NM, {}, accumulate)
