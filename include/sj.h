@@ -186,7 +186,9 @@ typedef struct sj_spec {
                                DRAM channels when rows are megabytes apart.
                                FP64 MFMA rows (LTimes, LPlusTimes and the fused pair): 1 = each lane
                                reads its operand rows from HBM, 2 = a group's rows move as flat runs
-                               through LDS (even D and NM); 0 = 2 where it fits.
+                               through LDS (even D and NM; odd ones where AUTO
+                               takes them, which sj_resolve returns with tile_k 16);
+                               0 = 2 where it fits.
                                SJ_SCATTERING, FP64 MFMA: 1 = tiles taken moments outer (a wave walks along z within a
                                moment), 2 = zone blocks outer (the tiles in flight together take the
                                moments of the same zones); 0 = the nesting's outer axis first (2 in

@@ -638,13 +638,22 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
             key.unroll = nfrag <= 32 ? 1 : 0;       // W fragments in registers (1) or LDS (0)
             if (!key.unroll && nfrag * 64 * 8 > 160 * 1024)
                 return fail(SJ_ERR_UNSUPPORTED, "MFMA weight fragments exceed 160 KiB of LDS");
-            // order 2: even row lengths, at most 32 16-byte loads per lane in flight, LDS within 160 KiB
+            // Odd row lengths as runs too, for many rows or an odd D (with order 2 on request where tile_k = 16,
+            // as sj_resolve returns it): read row by row, a quarter-wave touches 16 rows' lines in pieces that
+            // start anywhere.  Measured (LTimes / LPlusTimes, us, by rows against runs): 369,097 rows D=80
+            // NM=25 82.5/66.8 against 61.0/65.3, D=125 NM=9 106/121 against 76/77, D=89 NM=36 154/113 against
+            // 105/101, D=48 NM=9 35.2/30.2 against 33.6/32.3; 30,000 rows D=125 NM=9 11.3/14.9 against
+            // 11.7/8.9, D=80 NM=25 10.1/9.3 against 10.3/10.0; 9,001 rows D=127 NM=64 20/18 against 15/13.
+            const bool odd_runs = key.B >= 65536 || s->D % 2 != 0;
+            // order 2: even row lengths or the above, at most 32 (odd: 28, for the two values' places in the
+            // tile) 16-byte loads per lane in flight, LDS within 160 KiB
             auto run_ok = [&](int64_t rt, int block, const char **why) {
-                const int64_t pitch = std::max<int64_t>(16 * kb, outn) + 2;
+                const int64_t pitch = std::max<int64_t>(16 * kb, outn + outn % 2) + 2;
                 const int64_t lds = (int64_t)(block / 64) * 16 * rt * pitch * 8 + (key.unroll ? 0 : nfrag * 64 * 8);
-                if (red % 2 != 0 || outn % 2 != 0) return *why = "order 2 needs even D and NM", false;
+                if ((red % 2 != 0 || outn % 2 != 0) && !((s->order == 2 ? s->tile_k == 16 : odd_runs) && red * key.B >= 2))
+                    return *why = "order 2 needs even D and NM", false;
                 if (rt * ob * 4 > 96) return *why = "MFMA accumulators exceed 96 FP64 values per lane", false;
-                if ((16 * rt * red / 2 + 63) / 64 > 32) return *why = "order 2 holds at most 32 loads per lane", false;
+                if ((16 * rt * red / 2 + 63) / 64 > (red % 2 == 0 ? 32 : 28)) return *why = "order 2 holds at most 32 loads per lane", false;
                 if (lds > 160 * 1024) return *why = "order 2 tiles exceed 160 KiB of LDS", false;
                 return true;
             };

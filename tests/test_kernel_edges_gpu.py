@@ -199,3 +199,20 @@ def test_few_rows(P, orc, layout, Z, G, D, NM, accumulate):
         assert P.sj_specialize(k, **{f: r[f] for f in ("layout", "Z", "G", "D", "NM", "variant", "tile_n", "tile_k", "unroll",
                                                        "block", "order", "flags")}) == h
     test_columns(P, orc, layout, Z, G, D, NM, {}, accumulate)
+
+
+# odd row lengths as flat runs: pairs that straddle rows, one value past the last pair, rows that end
+# inside a group, outputs wider than the reduction's blocks
+@pytest.mark.parametrize("layout,Z,G,D,NM", [
+    ("ZGD", 9999, 1, 1, 1), ("GZD", 2733, 3, 5, 3), ("ZGD", 4097, 2, 33, 16), ("GZD", 8200, 1, 17, 31), ("ZGD", 8209, 1, 113, 9),
+    ("GZD", 21847, 3, 4, 3), ("ZGD", 65537, 1, 16, 25), ("ZDG", 65552, 1, 8, 1)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_odd_rows(P, orc, layout, Z, G, D, NM, accumulate):
+    for k in (P.SJ_LTIMES, P.SJ_LPLUSTIMES):
+        spec = dict(layout=layout, Z=Z, G=G, D=D, NM=NM)
+        h = P.sj_specialize(k, **spec)
+        assert "rows_mfma_lds" in P.sj_handle_info(h)["kernel_name"]
+        r = P.sj_resolve(k, **spec)
+        assert P.sj_specialize(k, **{f: r[f] for f in ("layout", "Z", "G", "D", "NM", "variant", "tile_n", "tile_k", "unroll",
+                                                       "block", "order", "flags")}) == h
+    test_columns(P, orc, layout, Z, G, D, NM, {}, accumulate)
