@@ -1,0 +1,47 @@
+"""What the library picks by itself: the default specializations fit the
+registers, can be launched, and lie in the tuner's set.  Compiled with
+SJ_FLAG_COMPILE_ONLY; nothing is launched."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# hiprtc comes with ROCm and, another version, with torch; the one loaded first serves the process
+_SCRATCH = """
+import json, sys
+if {torch}:
+    import torch
+from multiprocessing import Pool
+import paper_1904_08555_amd as P
+
+def one(spec):
+    spec = dict(spec)
+    k = getattr(P, spec.pop("kernel"))
+    h = P.sj_specialize(k, **dict(spec, flags=spec.get("flags", 0) | P.SJ_FLAG_COMPILE_ONLY))
+    return P.sj_handle_info(h)["scratch_bytes"]
+
+if __name__ == "__main__":
+    specs = json.load(sys.stdin)
+    with Pool(4) as p:
+        print(json.dumps([s for s, n in zip(specs, p.map(one, specs, chunksize=1)) if n != 0]))
+"""
+
+
+def spilling(specs, torch):
+    """The specs whose kernels use scratch (private memory)."""
+    r = subprocess.run([sys.executable, "-c", _SCRATCH.format(torch=torch)], input=json.dumps(specs), cwd=ROOT, text=True,
+                       capture_output=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+# the three sizes of column tiles (16,384 and 131,072 columns between them)
+@pytest.mark.parametrize("torch", [False, True])
+def test_columns_without_scratch(torch):
+    specs = [dict(kernel="SJ_LPLUSTIMES", layout="DGZ", Z=Z, G=2, D=D, NM=NM, flags=fl)
+             for Z in (8000, 40000, 70000) for D in (64, 96, 121, 128) for NM in (36, 49, 64) for fl in (0, 0x40)]
+    assert spilling(specs, torch) == []
