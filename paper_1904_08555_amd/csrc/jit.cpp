@@ -657,6 +657,16 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
                 if (lds > 160 * 1024) return *why = "order 2 tiles exceed 160 KiB of LDS", false;
                 return true;
             };
+            // Accumulating, a lane also holds its pairs of the group's old outputs, which fit beside the next group's
+            // loads and the accumulators up to about 268 registers, 284 where two tiles' pairs do not straddle rows
+            // (LPlusTimes, 369,097 rows, us with two 16-row tiles a wave (bytes of scratch) against one: NM = 25
+            // D = 112 143 (none) and 152, D = 113 206 (96) and 155, D = 125 257 (236) and 165; NM = 23 D = 126 147
+            // (none) and 165; operands read by the lanes instead where one tile is too much: D = 256, NM = 36
+            // 957 (12 at fewer rows) and 604, D = 384, NM = 16 2850 (400) and 539).
+            auto old_fit = [&](int64_t rt) {
+                const int64_t pairs = (16 * rt * red / 2 + 63) / 64 + (16 * rt * outn / 2 + 63) / 64;
+                return !(s->flags & SJ_FLAG_ACCUMULATE) || 4 * pairs + 8 * rt * ob <= (rt == 2 && outn % 2 == 0 ? 284 : 268);
+            };
             int order = s->order, rt = s->tile_n, block = s->block;
             const char *why = "";
             if (order != 1) {
@@ -666,9 +676,10 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
                 static const int kTry[3][2] = {{2, 256}, {1, 256}, {1, 64}};
                 int first = (red > outn || !key.unroll) ? 0 : 2;   // weights in LDS: share them over a wider block
                 bool found = false;
-                for (int i = first; i < 3 && !found; ++i) {
+                for (int i = first, fit = 1; i < 3 && !found; ++i) {
                     const int r = rt ? rt : kTry[i][0], b = block ? block : kTry[i][1];
-                    if (run_ok(r, b, &why)) { rt = r; block = b; found = true; }
+                    if ((!fit || old_fit(r)) && run_ok(r, b, &why)) { rt = r; block = b; found = true; }
+                    if (i == 2 && fit && order == 2) { fit = 0; i = first - 1; }   // asked for: also with scratch
                 }
                 if (!found && order == 2) return fail(SJ_ERR_UNSUPPORTED, why);
                 order = found ? 2 : 1;

@@ -8,6 +8,8 @@ import sys
 
 import pytest
 
+import paper_1904_08555_amd as P
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # hiprtc comes with ROCm and, another version, with torch; the one loaded first serves the process
@@ -45,3 +47,21 @@ def test_columns_without_scratch(torch):
     specs = [dict(kernel="SJ_LPLUSTIMES", layout="DGZ", Z=Z, G=2, D=D, NM=NM, flags=fl)
              for Z in (8000, 40000, 70000) for D in (64, 96, 121, 128) for NM in (36, 49, 64) for fl in (0, 0x40)]
     assert spilling(specs, torch) == []
+
+
+# accumulating rows, whose lanes also hold old outputs: around the line at which a wave takes one tile, and
+# beyond the longest rows of the flat form
+@pytest.mark.parametrize("torch", [False, True])
+def test_accumulating_rows_without_scratch(torch):
+    specs = [dict(kernel="SJ_LPLUSTIMES", layout="ZGD", Z=Z, G=1, D=D, NM=NM, flags=0x40)
+             for Z in (40000, 369097) for D, NM in ((112, 25), (112, 36), (113, 25), (117, 25), (125, 25), (127, 64), (128, 64),
+                                                    (256, 36), (273, 16), (384, 16))]
+    assert spilling(specs, torch) == []
+
+
+def test_accumulating_rows_on_request():
+    """Order 2 asked for stays accepted where it needs scratch, as before."""
+    for D, NM, tile in ((256, 36, {}), (384, 16, {}), (128, 16, dict(tile_n=2, block=64)), (384, 16, dict(tile_n=1, block=64))):
+        r = P.sj_resolve(P.SJ_LPLUSTIMES, layout="ZGD", Z=40000, G=1, D=D, NM=NM, variant=P.SJ_VAR_MFMA, order=2,
+                         flags=P.SJ_FLAG_ACCUMULATE, **tile)
+        assert r["order"] == 2
