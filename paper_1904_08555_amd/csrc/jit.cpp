@@ -218,6 +218,8 @@ static bool scattering_sorted_tile(int layout, int64_t Z, int64_t G, int64_t NM,
         // (1024 threads have 128 registers each: lines of an odd G, loaded value by value, with 16
         // fragments would spill)
         *block = G > 32 ? (G > 48 && G % 2 && !z_inner ? 512 : 1024) : lines > 131072 ? 512 : 256;
+        // a workgroup per 64 zones (from 1024 of them on, with all moments): a launch has to stay below 2^32 threads
+        if ((Z + 63) / 64 * *block >= int64_t(1) << 32) return false;
         if (G > 32) return !z_inner || lines <= 196608;
         return z_inner && ((G >= 31 && (lines <= 131072 || Z % 16 != 0)) || (G > 16 && lines <= 32768));
     }

@@ -65,3 +65,13 @@ def test_accumulating_rows_on_request():
         r = P.sj_resolve(P.SJ_LPLUSTIMES, layout="ZGD", Z=40000, G=1, D=D, NM=NM, variant=P.SJ_VAR_MFMA, order=2,
                          flags=P.SJ_FLAG_ACCUMULATE, **tile)
         assert r["order"] == 2
+
+
+# a launch of 2^32 threads or more is refused by the runtime: the largest scattering that sorts its zones by
+# material, one zone more, and 158 GB
+@pytest.mark.parametrize("layout", ["DZG", "ZDG", "GZD", "ZGD"])
+@pytest.mark.parametrize("Z,G", [(64 * (2 ** 22 - 1), 33), (64 * (2 ** 22 - 1) + 1, 33), (300000000, 33), (64 * (2 ** 23 - 1) + 1, 49)])
+def test_scattering_launch_limit(layout, Z, G):
+    h = P.sj_specialize(P.SJ_SCATTERING, layout=layout, Z=Z, G=G, NM=1, count=1, flags=P.SJ_FLAG_COMPILE_ONLY)
+    info = P.sj_handle_info(h)
+    assert 0 < info["grid"] * info["block"] < 2 ** 32
