@@ -179,6 +179,19 @@ static int64_t scattering_sorted_zone(int64_t G, int64_t NM)
     return n + (n % 2 == 0 ? 6 : 5);
 }
 
+// Whether neighbouring zones of a scattering nesting's arrays are neighbours in memory: by the strides, not
+// the nesting's name (with one moment GZD and GDZ are the same arrays)
+static bool scattering_z_inner(int layout, int64_t G, int64_t NM)
+{
+    switch (layout) {
+    case SJ_DGZ:
+    case SJ_GDZ: return true;
+    case SJ_DZG: return G == 1;
+    case SJ_GZD: return NM == 1;
+    default: return G == 1 && NM == 1;
+    }
+}
+
 // Scattering with zones sorted by material: whether SJ_VAR_AUTO takes it, with the zones per block
 // and the threads.  The other structures give a tile of matrix products, or a wave of lines, one
 // material and form the outputs again for each material they meet, so their time depends on how the
@@ -189,7 +202,8 @@ static int64_t scattering_sorted_zone(int64_t G, int64_t NM)
 //   z innermost, G > 32: a line per thread needs about three waves per SIMD to hide its matrix
 //     reads, so up to 196608 lines (Z=5003 G=40 NM=9 18.7/22 against 22.5/69, Z=2003 G=60 NM=4
 //     9/10.7 against 125/157).  More lines in zone order are faster by the thread (DGZ Z=20011 G=44
-//     NM=16 85/100 against 69/450).
+//     NM=16 85/100 against 69/450), but not in GZD, with one moment the same arrays, whose threads take
+//     two zones (Z=250000 G=44, caches emptied, 85/103 against 98/320).
 //   G 17 ... 32 (before: matrix-core tiles of one moment and 16 zones): z innermost, where there are
 //     few waves of tiles (Z=1003 G=32 NM=9 6.7/7.7 against 10.9/34) or, at G = 31 and 32, rows that
 //     are no whole lines (Z=23855 G=32 NM=16 66/77 against 73/188).  Whole lines: 65/80 against
@@ -213,14 +227,14 @@ static bool scattering_sorted_tile(int layout, int64_t Z, int64_t G, int64_t NM,
     const bool nm_inner = (layout == SJ_GZD || layout == SJ_ZGD) && NM > 1;
     if (!nm_inner) {
         const int64_t lines = NM * Z;
-        const bool z_inner = layout == SJ_DGZ || layout == SJ_GDZ;
+        const bool z_inner = scattering_z_inner(layout, G, NM);
         *zb = 64;
         // (1024 threads have 128 registers each: lines of an odd G, loaded value by value, with 16
         // fragments would spill)
         *block = G > 32 ? (G > 48 && G % 2 && !z_inner ? 512 : 1024) : lines > 131072 ? 512 : 256;
         // a workgroup per 64 zones (from 1024 of them on, with all moments): a launch has to stay below 2^32 threads
         if ((Z + 63) / 64 * *block >= int64_t(1) << 32) return false;
-        if (G > 32) return !z_inner || lines <= 196608;
+        if (G > 32) return !z_inner || lines <= 196608 || layout == SJ_GZD;
         return z_inner && ((G >= 31 && (lines <= 131072 || Z % 16 != 0)) || (G > 16 && lines <= 32768));
     }
     if (NM > 64 || G < 8 || (layout == SJ_GZD && G <= 32 && Z * NM % 8192 == 0)) return false;
@@ -1182,18 +1196,21 @@ static const char *kCommonPrologue =
 //   stores, z innermost, rows that start off a half line: a wave's 128-byte pieces then share lines with
 //     its neighbours' (DGZ Z=50011 G=24 NM=16 178/120, Z=23855 G=32 108/60, Z=150001 G=6 126/76; half lines,
 //     Z=20008, 33/50);
-//   ZDG, lines of less than 128 bytes apart from one another: both (Z=60001 G=5 NM=16 60/33, Z=20011 G=15
-//     31/23), and loads of lines that are no multiple of 128 bytes (Z=50011 G=31 132/120).
+//   g innermost, lines of less than 128 bytes, ZDG (where a moment's lie apart from one another): both
+//     (Z=60001 G=5 NM=16 60/33, Z=20011 G=15 31/23), and loads of lines that are no multiple of 128 bytes
+//     (Z=50011 G=31 132/120).  One moment, whose lines are contiguous in DZG, ZDG and ZGD alike, beyond
+//     160 MB (DZG Z=1000000 G=15 55/44, Z=500001 G=31 63/54; 24 MB, Z=300000 G=5 12.9/13.8).
 static void scattering_policy(const SpecKey &k, int *nt_load, int *nt_store)
 {
     int ntl = 1, nts = 1;
     if (k.variant == SJ_VAR_MFMA || scattering_sorted(k)) {
-        const bool z_inner = k.layout == SJ_DGZ || k.layout == SJ_GDZ;
+        const bool z_inner = scattering_z_inner(k.layout, k.G, k.NM);
+        const bool lines = !z_inner && (k.NM == 1 ? 16 * k.G * k.Z > 160000000 : k.layout == SJ_ZDG);
         if (16 * k.NM * k.G * k.Z <= 160000000) ntl = 0;
         if (k.variant == SJ_VAR_MFMA) {
             if (z_inner && k.Z % 8 != 0) nts = 0;
-            if (k.layout == SJ_ZDG && k.G % 16 != 0) ntl = 0;
-            if (k.layout == SJ_ZDG && k.G < 16) nts = 0;
+            if (lines && k.G % 16 != 0) ntl = 0;
+            if (lines && k.G < 16) nts = 0;
         }
     }
     if (k.flags & SJ_FLAG_LOADS_CACHED) ntl = 0;

@@ -75,3 +75,17 @@ def test_scattering_launch_limit(layout, Z, G):
     h = P.sj_specialize(P.SJ_SCATTERING, layout=layout, Z=Z, G=G, NM=1, count=1, flags=P.SJ_FLAG_COMPILE_ONLY)
     info = P.sj_handle_info(h)
     assert 0 < info["grid"] * info["block"] < 2 ** 32
+
+
+# one moment: DGZ, GDZ and GZD are the same arrays, and so are DZG, ZDG and ZGD, on both sides of the rules' lines
+@pytest.mark.parametrize("Z,G", [(196608, 44), (30000, 24), (1000, 33), (5000, 55), (1001, 17), (300001, 24), (300000, 5), (1000000, 15),
+                                 (500001, 31), (2000003, 5)])
+def test_scattering_one_moment(Z, G):
+    for same in (("DGZ", "GDZ", "GZD"), ("DZG", "ZDG", "ZGD")):
+        picks = set()
+        for layout in same:
+            spec = dict(layout=layout, Z=Z, G=G, NM=1, count=3)
+            r = P.sj_resolve(P.SJ_SCATTERING, **spec)
+            src = P.sj_emit_source(P.SJ_SCATTERING, **spec)
+            picks.add((r["variant"], r["tile_k"]) + tuple("#define SJ_NT_%s 1" % w in src for w in ("LOAD", "STORE")))
+        assert len(picks) == 1, (same, picks)
