@@ -399,6 +399,7 @@ sj_status make_key(sj_kernel k, const sj_spec *s, int device, const char *arch, 
     for (int i = 0; i < n; ++i) {
         sj_spec t = *s;
         t.variant = order[i];
+        if (I == 1 && t.variant == SJ_VAR_MFMA) t.tile_k = 0;   // names a form where the structure is named too
         int ct = 0, cblock = 0;
         if (k == SJ_LTIMES_LPLUS && t.variant == SJ_VAR_DIRECT && t.tile_n == 0 && t.unroll == 0 && t.block == 0 && t.order == 0 &&
             fused_cols_tile(B, I, t.NM, &ct, &cblock))
@@ -666,7 +667,7 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
             auto run_ok = [&](int64_t rt, int block, const char **why) {
                 const int64_t pitch = std::max<int64_t>(16 * kb, outn + outn % 2) + 2;
                 const int64_t lds = (int64_t)(block / 64) * 16 * rt * pitch * 8 + (key.unroll ? 0 : nfrag * 64 * 8);
-                if ((red % 2 != 0 || outn % 2 != 0) && !((s->order == 2 ? s->tile_k == 16 : odd_runs) && red * key.B >= 2))
+                if ((red % 2 != 0 || outn % 2 != 0) && !(odd_runs && (s->order != 2 || s->tile_k == 16) && red * key.B >= 2))
                     return *why = "order 2 needs even D and NM", false;
                 if (rt * ob * 4 > 96) return *why = "MFMA accumulators exceed 96 FP64 values per lane", false;
                 if ((16 * rt * red / 2 + 63) / 64 > (red % 2 == 0 ? 32 : 28)) return *why = "order 2 holds at most 32 loads per lane", false;

@@ -89,3 +89,29 @@ def test_scattering_one_moment(Z, G):
             src = P.sj_emit_source(P.SJ_SCATTERING, **spec)
             picks.add((r["variant"], r["tile_k"]) + tuple("#define SJ_NT_%s 1" % w in src for w in ("LOAD", "STORE")))
         assert len(picks) == 1, (same, picks)
+
+
+def refused(kernel, **spec):
+    try:
+        P.sj_resolve(kernel, **spec)
+    except P.SJError as e:
+        return e.status in (P.SJ_ERR_UNSUPPORTED, P.SJ_ERR_INVALID_ARG)
+    return False
+
+
+# flat runs of odd rows: named by tile_k 16 with MFMA where AUTO takes them, and there only
+@pytest.mark.parametrize("layout,Z,D,NM,taken", [("ZGD", 40, 63, 45, True), ("ZGD", 40, 12, 45, False), ("GZD", 65535, 16, 9, False),
+                                                 ("ZGD", 65536, 16, 9, True), ("GZD", 9000, 17, 31, True)])
+def test_odd_runs_on_request(layout, Z, D, NM, taken):
+    for k in (P.SJ_LTIMES, P.SJ_LPLUSTIMES):
+        spec = dict(layout=layout, Z=Z, G=1, D=D, NM=NM, order=2)
+        assert refused(k, **spec) and refused(k, variant=P.SJ_VAR_MFMA, **spec)
+        assert refused(k, tile_k=16, **spec)                 # AUTO has no structure for the field to name
+        assert refused(k, variant=P.SJ_VAR_MFMA, tile_k=16, **spec) != taken
+
+
+def test_few_rows_form_is_named_with_its_structure():
+    """tile_k 4 names the column form of few rows with MFMA; with AUTO it is STAGED's field, as it was."""
+    spec = dict(layout="ZGD", Z=100, G=1, D=96, NM=16, tile_n=1, unroll=8, block=64, order=1, tile_k=4)
+    assert P.sj_resolve(P.SJ_LTIMES, variant=P.SJ_VAR_MFMA, **spec)["tile_k"] == 4
+    assert P.sj_resolve(P.SJ_LTIMES, **spec)["tile_k"] == 16
