@@ -172,7 +172,8 @@ typedef struct sj_spec {
                                per workgroup with which AUTO sorts zones by material, where it does;
                                fused, DIRECT, column layouts: the columns per workgroup of AUTO's
                                matrix-core form, where it takes it; MFMA, D innermost, few rows:
-                               4 = AUTO's column form (all as sj_resolve returns them);
+                               4 = AUTO's column form; SJ_MASS: 1 = the staged form at the workgroup
+                               form's tile (all as sj_resolve returns them);
                                0 = default */
     int32_t  unroll;        /* DIRECT: reduction steps whose loads are issued before their FMAs;
                                FP64 MFMA columns: 4-deep reduction steps per group of loads in flight
@@ -292,9 +293,12 @@ sj_status sj_specialize_with_code(sj_kernel k, const sj_spec *spec, const void *
  *                  spec->D = D1D (dofs per direction, 1..32), spec->NM = Q1D (points per direction, 1..32),
  *                  spec->inputs = dim (1, 2, 3), spec->count = NE (elements); B1 row-major [Q1D][D1D] (the
  *                  1-D basis at the points); per element the first index component is fastest; tile_n =
- *                  elements per wave (0 = default; hexahedra with Q1D >= 4 other than 6 are taken by
- *                  whole workgroups by default, and tile_n is then the elements of a workgroup).  y_e = B^T diag(D_e) B x_e, B the dim-fold tensor
- *                  product of B1 (the Laghos-style partial-assembly mass action); overwrites Y.
+ *                  elements per wave (0 = default), order = 1 (a wave's elements staged in LDS) or 2
+ *                  (pipelined waves).  Hexahedra with Q1D >= 4 other than 6 are taken by whole workgroups by
+ *                  default (order 1 with tile_n, the elements of a workgroup, and block, as sj_resolve returns
+ *                  them; the kernel is then named sj_mass_pa_hex_*); order 1 without both is the staged form,
+ *                  and so it is at that very tile with tile_k = 1.  y_e = B^T diag(D_e) B x_e, B the dim-fold
+ *                  tensor product of B1 (the Laghos-style partial-assembly mass action); overwrites Y.
  *   SJ_MLP_FWD:    {theta f32, X [rows*inputs] f32, y [rows] f32}
  *   SJ_MLP_BWD:    {theta f32, X [rows*inputs] f32, t [rows] f32, grad f32 (same packing as theta), loss [1] f32,
  *                  workspace [rows*(4*width+2)] f32}

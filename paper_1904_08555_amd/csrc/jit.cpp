@@ -440,8 +440,8 @@ static bool mass_hex_tile(int64_t D, int64_t Q, int64_t ne, int *ew, int *block)
 static bool mass_hex(const SpecKey &k)
 {
     int ew = 0, block = 0;
-    return k.kernel == SJ_MASS && k.order == 1 && k.inputs == 3 && mass_hex_tile(k.D, k.NM, k.rows, &ew, &block) &&
-           k.tile_n == ew && k.block == block;
+    return k.kernel == SJ_MASS && k.order == 1 && k.inputs == 3 && k.tile_k == 0 &&
+           mass_hex_tile(k.D, k.NM, k.rows, &ew, &block) && k.tile_n == ew && k.block == block;
 }
 
 static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const char *arch, SpecKey *out)
@@ -767,7 +767,8 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
         if (s->count < 1 || s->count > (int64_t(1) << 31) - 1) return fail(SJ_ERR_INVALID_ARG, "count (elements) must be in [1, 2^31-1]");
         if (s->variant != SJ_VAR_AUTO && s->variant != SJ_VAR_DIRECT)
             return fail(SJ_ERR_UNSUPPORTED, "the mass operator has the DIRECT structure only");
-        if (s->tile_k != 0 || s->unroll != 0 || s->order < 0 || s->order > 2 || (s->flags & SJ_FLAG_ACCUMULATE))
+        if (s->tile_k < 0 || s->tile_k > 1 || s->unroll != 0 || s->order < 0 || s->order > 2 || (s->tile_k == 1 && s->order != 1) ||
+            (s->flags & SJ_FLAG_ACCUMULATE))
             return fail(SJ_ERR_INVALID_ARG, "the mass operator takes tile_n, block and order (0, 1, 2) only");
         // order 1: one group of elements per wave, x and D staged in LDS; order 2: persistent waves
         // that load the next group into registers while computing the current one (D stays in
@@ -803,17 +804,23 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
         int block = s->block;
         if (block == 0) block = (order == 2) ? 64 : (lds(128) <= 64 * 1024) ? 128 : 64;
         if (!valid_block(block)) return fail(SJ_ERR_INVALID_ARG, "block must be a multiple of 64 in [64, 1024]");
-        // the hexahedra's workgroup form by default, or where order 1 names its tile and block
+        // the hexahedra's workgroup form by default, or where order 1 names its tile and block; accepted
+        // where the form that any other request gets by default is (hexahedra: one element a wave, 64 threads)
         int hew = 0, hblock = 0;
         const bool hex = dim == 3 && mass_hex_tile(D1D, Q1D, s->count, &hew, &hblock);
-        const bool hex_named = hex && s->order == 1 && s->tile_n == hew && s->block == hblock;
-        if (!hex_named && lds(block) > 160 * 1024)
+        const bool named = s->order == 1 && s->tile_n == hew && s->block == hblock && s->tile_k == 0;
+        const bool take_hex = hex && (named || (s->order == 0 && s->tile_n == 0 && s->block == 0));
+        if (take_hex ? (2 * ns + nq) * 8 > 160 * 1024 : lds(block) > 160 * 1024)
             return fail(SJ_ERR_UNSUPPORTED, "mass operator tiles exceed 160 KiB of LDS");
-        if (hex && s->order == 0 && s->tile_n == 0 && s->block == 0) {
+        if (take_hex) {
             order = 1;
             ew = hew;
             block = hblock;
+        } else if (hex && order == 1 && ew == hew && block == hblock) {
+            key.tile_k = 1;   // the staged form at the workgroup form's tile
         }
+        if (s->tile_k != key.tile_k && s->tile_k != 0)
+            return fail(SJ_ERR_INVALID_ARG, "mass operator: tile_k is 0, or 1 for the staged form at the workgroup form's tile");
         if (s->count * std::max(nd, nq) > (int64_t(1) << 50)) return fail(SJ_ERR_INVALID_ARG, "arrays too large");
         key.D = D1D; key.NM = Q1D; key.inputs = dim; key.rows = s->count;
         key.tile_n = ew; key.block = block; key.variant = SJ_VAR_DIRECT; key.order = order;
@@ -1384,7 +1391,7 @@ sj_status emit_source(const SpecKey &k, std::string *src, std::string *name, std
           << ((k.flags & SJ_FLAG_LOADS_CACHED) ? 0 : 1) << "\n#define SJ_NT_STORE " << ((k.flags & SJ_FLAG_STORES_CACHED) ? 0 : 1)
           << "\n#define SJ_ACCUM 0\n";
         body = (k.order == 2) ? kTpl_mass_pa_pipe : mass_hex(k) ? kTpl_mass_pa_hex : kTpl_mass_pa;
-        *name = std::string(k.order == 2 ? "sj_mass_pa_pipe_" : "sj_mass_pa_") + std::to_string(k.inputs) + "d_d" +
+        *name = std::string(k.order == 2 ? "sj_mass_pa_pipe_" : mass_hex(k) ? "sj_mass_pa_hex_" : "sj_mass_pa_") + std::to_string(k.inputs) + "d_d" +
                 std::to_string(k.D) + "_q" + std::to_string(k.NM);
         o << "#define SJ_KERNEL_NAME " << *name << "\n";
     }

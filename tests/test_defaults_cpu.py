@@ -115,3 +115,32 @@ def test_few_rows_form_is_named_with_its_structure():
     spec = dict(layout="ZGD", Z=100, G=1, D=96, NM=16, tile_n=1, unroll=8, block=64, order=1, tile_k=4)
     assert P.sj_resolve(P.SJ_LTIMES, variant=P.SJ_VAR_MFMA, **spec)["tile_k"] == 4
     assert P.sj_resolve(P.SJ_LTIMES, **spec)["tile_k"] == 16
+
+
+def mass(**kw):
+    spec = dict(dict(D=8, NM=12, inputs=3, count=20000), **kw)
+    r = P.sj_resolve(P.SJ_MASS, **spec)
+    named = {f: r[f] for f in ("tile_n", "tile_k", "block", "order")}
+    assert P.sj_emit_source(P.SJ_MASS, **dict(spec, **named)) == P.sj_emit_source(P.SJ_MASS, **spec)
+    return P.sj_handle_info(P.sj_specialize(P.SJ_MASS, **dict(spec, flags=P.SJ_FLAG_COMPILE_ONLY)))["kernel_name"]
+
+
+# order 1 is the staged form of a wave's elements, also where its default tile (one element, 128 threads) is
+# the workgroup form's; that is the default, and order 1 with its tile and block
+@pytest.mark.parametrize("D,Q", [(8, 12), (9, 9), (2, 14), (5, 10)])
+def test_mass_forms_by_name(D, Q):
+    hexa, staged = "sj_mass_pa_hex_3d_d%d_q%d" % (D, Q), "sj_mass_pa_3d_d%d_q%d" % (D, Q)
+    assert mass(D=D, NM=Q) == hexa and mass(D=D, NM=Q, order=1, tile_n=1, block=128) == hexa
+    for other in (dict(order=1), dict(order=1, tile_n=1), dict(order=1, block=128), dict(order=1, block=64),
+                  dict(order=1, tile_n=1, block=128, tile_k=1)):
+        assert mass(D=D, NM=Q, **other) == staged, other
+    for refused_ in (dict(tile_k=1), dict(order=2, tile_k=1), dict(order=1, block=64, tile_k=1), dict(order=1, tile_k=2),
+                     dict(order=1, tile_k=-1), dict(inputs=2, order=1, tile_k=1)):
+        assert refused(P.SJ_MASS, D=D, NM=Q, **dict(dict(inputs=3, count=20000), **refused_)), refused_
+
+
+def test_mass_range_is_one_for_every_request():
+    """Elements too large for the staged form's LDS are refused, also where the workgroup form is named."""
+    for spec in ({}, dict(order=1), dict(order=1, tile_n=1, block=512)):
+        assert refused(P.SJ_MASS, D=19, NM=19, inputs=3, count=3, **spec), spec
+        assert not refused(P.SJ_MASS, D=18, NM=18, inputs=3, count=3, **spec), spec
