@@ -36,6 +36,10 @@ uint64_t mix64(uint64_t z)
 
 constexpr int64_t kMaxDim = 2147483647;  // each size <= 2^31 - 1
 
+// arrays from here on take 64-bit indexes: 2^31 elements, less what a kernel's last tile or group of
+// elements may reach past the last one before it is clamped (at most 14,336 elements)
+constexpr int64_t kIndex64 = (int64_t(1) << 31) - 65536;
+
 }  // namespace
 
 sj_status fail(sj_status s, const std::string &msg)
@@ -499,7 +503,7 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
         key.Z = s->Z; key.G = s->G; key.D = s->D; key.NM = s->NM;
         layout_view(s->layout, s->Z, s->G, &key.B, &key.I);
         const int64_t nelem = cols * maxa;
-        key.index64 = (nelem >= (int64_t(1) << 31) || (s->flags & SJ_FLAG_INDEX64)) ? 1 : 0;
+        key.index64 = (nelem >= kIndex64 || (s->flags & SJ_FLAG_INDEX64)) ? 1 : 0;
 
         int var = s->variant;
         if (var == SJ_VAR_AUTO) {
@@ -824,7 +828,7 @@ static sj_status make_key_one(sj_kernel k, const sj_spec *s, int device, const c
         if (s->count * std::max(nd, nq) > (int64_t(1) << 50)) return fail(SJ_ERR_INVALID_ARG, "arrays too large");
         key.D = D1D; key.NM = Q1D; key.inputs = dim; key.rows = s->count;
         key.tile_n = ew; key.block = block; key.variant = SJ_VAR_DIRECT; key.order = order;
-        key.index64 = (s->count * std::max(nd, nq) >= (int64_t(1) << 31) || (s->flags & SJ_FLAG_INDEX64)) ? 1 : 0;
+        key.index64 = (s->count * std::max(nd, nq) >= kIndex64 || (s->flags & SJ_FLAG_INDEX64)) ? 1 : 0;
         return (*out = key), SJ_OK;
     }
     if (k == SJ_SCATTERING) {

@@ -144,3 +144,15 @@ def test_mass_range_is_one_for_every_request():
     for spec in ({}, dict(order=1), dict(order=1, tile_n=1, block=512)):
         assert refused(P.SJ_MASS, D=19, NM=19, inputs=3, count=3, **spec), spec
         assert not refused(P.SJ_MASS, D=18, NM=18, inputs=3, count=3, **spec), spec
+
+
+# arrays whose last element is near 2^31 while a tile or group of elements reaches past it
+@pytest.mark.parametrize("kernel,spec", [
+    ("SJ_LTIMES", dict(layout="ZDG", Z=536870911, G=4, D=1, NM=1)), ("SJ_LPLUSTIMES", dict(layout="ZDG", Z=306783378, G=7, D=1, NM=1)),
+    ("SJ_LTIMES", dict(layout="ZGD", Z=2147483647, G=1, D=1, NM=1)), ("SJ_LPLUSTIMES", dict(layout="GZD", Z=2147483617, G=1, D=1, NM=1)),
+    ("SJ_LTIMES", dict(layout="ZGD", Z=715827882, G=1, D=3, NM=1)), ("SJ_MASS", dict(D=8, NM=4, inputs=3, count=4194303)),
+    ("SJ_MASS", dict(D=2, NM=14, inputs=3, count=782610))])
+def test_largest_arrays(kernel, spec):
+    k = getattr(P, kernel)
+    P.sj_specialize(k, flags=P.SJ_FLAG_COMPILE_ONLY, **spec)
+    assert "typedef long long sj_index_t" in P.sj_emit_source(k, **spec)
