@@ -101,8 +101,8 @@ def features(shape: dict, cand: dict) -> np.ndarray:
     I = contiguous_extent(lay, Z, G)
     B = G * Z // I
     var, tn, blk = r["variant"], max(1, r["tile_n"]), r["block"]
-    col_mfma = var == sj.SJ_VAR_MFMA and f64 and I > 1
-    row_mfma = var == sj.SJ_VAR_MFMA and f64 and I == 1
+    col_mfma = var == sj.SJ_VAR_MFMA and f64 and r["tile_k"] == 4     # few rows too, as columns one value apart
+    row_mfma = var == sj.SJ_VAR_MFMA and f64 and not col_mfma
     f[0:4] = [math.log2(Z), math.log2(G), math.log2(D), math.log2(NM)]
     f[4] = 1.0 if f64 else 0.0
     f[5] = 1.0 - f[4]
@@ -130,7 +130,8 @@ def features(shape: dict, cand: dict) -> np.ndarray:
     f[24] = math.log2((D + NM) * G * Z * esz)             # algorithmic bytes
     f[25] = math.log2(2.0 * D * NM * G * Z)               # flops
     f[26] = math.log2(I * esz) if lay in ("DGZ", "DZG") else math.log2(Z * esz)  # row stride proxy
-    f[27] = I / (((I + width - 1) // width) * width) if width > 1 else 1.0       # lanes holding a real column
+    run = B * I if col_mfma else I                        # columns tiled together
+    f[27] = run / (((run + width - 1) // width) * width) if width > 1 else 1.0   # lanes holding a real column
     f[28] = math.log2(B)
     f[29] = math.log2(max(1, acc))                        # accumulators per lane
     f[30] = r["tile_k"] / 32.0 if var == sj.SJ_VAR_STAGED else 0.0

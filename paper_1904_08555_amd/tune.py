@@ -7,7 +7,7 @@ runs), times each one with sj_time_run, and returns the fastest together with
 every timing.  This is the profile-guided autotuning named as future work in
 ClangJIT section 6; it is also the reference the learned picker is measured against.
 
-The candidate set (at most 35 per kernel and layout):
+The candidate set (at most 36 per kernel and layout):
   * innermost axis is a column axis (DGZ, DZG, GDZ, ZDG):
     DIRECT with tile_n (columns per thread) in {1, 2} dividing the contiguous
     extent, unroll in {4, 8, 16}, block in {256, 512}, order in {ascending,
@@ -23,6 +23,8 @@ The candidate set (at most 35 per kernel and layout):
     range of each sweep); DIRECT with tile_n 1, unroll 8  (<= 35)
   * BF16 dtypes: columns per lane in {1, 4} (4 when it divides the extent),
     block in {256, 512}  (<= 4)
+  * what the library takes by itself (SJ_VAR_AUTO, as sj_resolve returns it),
+    where it is none of these
 Candidates that the specializer rejects for a shape (register or LDS limits)
 are reported as rejected; candidates that resolve to the same specialization
 as an earlier one are dropped.
@@ -108,6 +110,7 @@ def contiguous_extent(layout: str, Z: int, G: int) -> int:
 
 def candidates(kernel: int, layout: str, Z: int, G: int, D: int, NM: int, dtype: int = sj.SJ_F64) -> list:
     out = []
+    base = dict(layout=layout, Z=Z, G=G, D=D, NM=NM, dtype=dtype)
     ext = contiguous_extent(layout, Z, G)
     if dtype != sj.SJ_F64:
         for cpl in (1, 4):
@@ -115,7 +118,7 @@ def candidates(kernel: int, layout: str, Z: int, G: int, D: int, NM: int, dtype:
                 continue
             for block in (256, 512):
                 out.append(dict(variant=sj.SJ_VAR_MFMA, tile_n=cpl, block=block))
-        return distinct(kernel, dict(layout=layout, Z=Z, G=G, D=D, NM=NM, dtype=dtype), out)
+        return distinct(kernel, base, out + default(kernel, base))
     if ext > 1:
         for vec in (1, 2):
             if ext % vec:
@@ -142,7 +145,17 @@ def candidates(kernel: int, layout: str, Z: int, G: int, D: int, NM: int, dtype:
                 for xcd in (sj.SJ_FLAG_XCD_INTERLEAVED, sj.SJ_FLAG_XCD_CONTIGUOUS):
                     out.append(dict(variant=sj.SJ_VAR_MFMA, tile_n=rt, block=block, order=2, flags=fl | xcd))
         out.append(dict(variant=sj.SJ_VAR_DIRECT, tile_n=1, unroll=8, block=256))
-    return distinct(kernel, dict(layout=layout, Z=Z, G=G, D=D, NM=NM, dtype=dtype), out)
+    return distinct(kernel, base, out + default(kernel, base))
+
+
+def default(kernel: int, base: dict) -> list:
+    """The structure and tiles that the library takes for a request that names
+    none, as a candidate (empty where it refuses the shape)."""
+    try:
+        r = sj.sj_resolve(kernel, **base)
+    except sj.SJError:
+        return []
+    return [{f: r[f] for f in ("variant", "tile_n", "tile_k", "unroll", "block", "order") if r[f]}]
 
 
 def distinct(kernel: int, base: dict, cands: list) -> list:

@@ -9,6 +9,7 @@ import sys
 import pytest
 
 import paper_1904_08555_amd as P
+from paper_1904_08555_amd import picker, tune
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -156,3 +157,32 @@ def test_largest_arrays(kernel, spec):
     k = getattr(P, kernel)
     P.sj_specialize(k, flags=P.SJ_FLAG_COMPILE_ONLY, **spec)
     assert "typedef long long sj_index_t" in P.sj_emit_source(k, **spec)
+
+
+# the tuner's set holds what the library takes by itself, so that tuning never returns something slower than
+# not tuning: on both sides of the rules' lines
+@pytest.mark.parametrize("Z,G,D,NM", [(3001, 1, 96, 36), (4096, 8, 48, 16), (32768, 32, 96, 16), (20000, 2, 128, 64), (65538, 2, 16, 64),
+                                      (1800, 6, 24, 16), (8300, 2, 27, 9), (17576, 21, 80, 25), (64, 9, 16, 1), (512, 3, 113, 36)])
+def test_tuner_holds_the_default(Z, G, D, NM):
+    for k in (P.SJ_LTIMES, P.SJ_LPLUSTIMES):
+        for layout in P.LAYOUTS:
+            spec = dict(layout=layout, Z=Z, G=G, D=D, NM=NM)
+            cands = tune.candidates(k, layout, Z, G, D, NM)
+            want = P.sj_emit_source(k, **spec)
+            assert any(want == P.sj_emit_source(k, **spec, **c) for c in tune.distinct(k, spec, cands)
+                       if not refused(k, **spec, **c)), (k, layout)
+
+
+def test_tuner_holds_the_bf16_default():
+    spec = dict(layout="DGZ", Z=4096, G=8, D=48, NM=16, dtype=P.SJ_BF16X3)
+    want = P.sj_emit_source(P.SJ_LTIMES, **spec)
+    assert want in [P.sj_emit_source(P.SJ_LTIMES, **spec, **c) for c in tune.candidates(P.SJ_LTIMES, "DGZ", 4096, 8, 48, 16, P.SJ_BF16X3)]
+
+
+def test_features_of_few_rows():
+    """Few rows as columns are described as the column kernel that runs, with full tiles."""
+    s = dict(Z=3000, G=1, D=96, NM=36, dtype=P.SJ_F64)
+    f = picker.features(s, dict(layout="ZGD"))
+    assert (f[15], f[16]) == (1.0, 0.0) and f[27] == 3000 / 3008
+    f = picker.features(s, dict(layout="ZGD", variant=P.SJ_VAR_MFMA))
+    assert (f[15], f[16]) == (0.0, 1.0)
