@@ -107,9 +107,11 @@ typedef enum sj_dtype {
  * line measured on MI355X (about 131,072 columns, 65,536 where the contiguous
  * extent is no multiple of 16; any number with more than 48 moments; DIRECT
  * where a tile field of the spec is set); the FP64 matrix-core row kernel
- * (MFMA) when it is D (GZD, ZGD); BF16 dtypes always use MFMA.  The fused
- * SJ_LTIMES_LPLUS has DIRECT and, for D innermost, the MFMA row structure
- * (AUTO's choice there).  When AUTO's first choice declines a shape (register
+ * (MFMA) when it is D (GZD, ZGD), up to 4,096 or 8,192 rows the column kernel
+ * on them; BF16 dtypes always use MFMA.  The fused
+ * SJ_LTIMES_LPLUS has DIRECT (few columns: on the matrix cores, which tile_k
+ * of sj_resolve and sj_handle_info tells) and, for D innermost, the MFMA row
+ * structure (AUTO's choice there).  When AUTO's first choice declines a shape (register
  * or LDS limits), the next structure that accepts it is taken. */
 typedef enum sj_variant {
     SJ_VAR_AUTO = 0,
@@ -118,12 +120,13 @@ typedef enum sj_variant {
     SJ_VAR_MFMA = 3      /* matrix cores: BF16 dtypes; FP64 row kernel (D innermost) or column kernel;
                             SJ_SCATTERING: FP64 tiles of one moment and 16 zones (the default where
                             g or z is innermost, G <= 32 and the lines are many; with nm innermost,
-                            16-zone blocks staged in LDS); AUTO elsewhere sorts zones by material */
+                            16-zone blocks staged in LDS); AUTO elsewhere sorts zones by material
+                            (a DIRECT handle with tile_k != 0) */
 } sj_variant;
 
 /* Flags. */
 #define SJ_FLAG_COMPILE_ONLY      0x1u  /* compile to a code object, do not load: no GPU needed; the handle cannot run */
-#define SJ_FLAG_INDEX64           0x2u  /* force 64-bit indexing (chosen automatically when an array has >= 2^31 elements) */
+#define SJ_FLAG_INDEX64           0x2u  /* force 64-bit indexing (chosen automatically from about 2^31 elements an array on) */
 #define SJ_FLAG_LOADS_CACHED      0x4u  /* LTimes / LPlusTimes: ordinary loads of the streamed input */
 #define SJ_FLAG_LOADS_NONTEMPORAL 0x8u  /* LTimes / LPlusTimes: nontemporal loads of the streamed input */
 #define SJ_FLAG_STORES_CACHED     0x10u /* LTimes / LPlusTimes: ordinary stores of the output */
@@ -131,14 +134,17 @@ typedef enum sj_variant {
 #define SJ_FLAG_ACCUMULATE        0x40u /* LTimes / LPlusTimes: add the result to the output's current values
                                            (phi += L psi, psi' += L+ phi: several direction sets summed into one
                                            output) instead of overwriting; the output is then also read */
-/* Without a loads flag (stores flag) the default measured on MI355X applies:
- * nontemporal stores for LPlusTimes and the row kernels; ordinary stores of
- * LTimes' moments where they exceed what the caches hold anyway (LPlusTimes
- * reads them next), and where rows are no multiple of a 128-byte line;
- * nontemporal loads for LTimes' column kernels and for large LPlusTimes column
- * kernels, ordinary loads for the FP64 MFMA row kernel.  The two flags of a
- * pair exclude each other; every policy flag is part of the specialization
- * key. */
+/* Without a loads flag (stores flag) the default measured on MI355X applies.
+ * Stores: nontemporal for the row kernels and LPlusTimes; ordinary for the
+ * moments of LTimes' column kernels where both arrays together pass 32 MB
+ * (LPlusTimes, which reads them next, finds them in the last-level cache), for
+ * most column kernels whose rows are no multiple of a 128-byte line, for few
+ * rows as columns and for the BF16 row form.  Loads: nontemporal for LTimes'
+ * column kernels and its LDS-staged rows, and for LPlusTimes' columns with
+ * more than 48 moments and over 32 MB; ordinary for LPlusTimes' other columns
+ * and rows, and for LTimes' rows read by the lanes.  sj_resolve returns both
+ * choices.  The two flags of a pair exclude each other; every policy flag is
+ * part of the specialization key. */
 #define SJ_FLAG_GENERIC_PER_LAYOUT 0x80u /* sj_generic_run, LTimes / LPlusTimes: the kernel compiled ahead of time
                                            for the spec's nesting (sizes still run-time arguments), Kripke's
                                            multiversioning; without it one kernel serves every nesting */

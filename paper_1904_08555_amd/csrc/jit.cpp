@@ -155,7 +155,8 @@ static int64_t cols_tiles(const SpecKey &k)
 // a tile's 16-output blocks until there are about four waves a CU, at most four blocks each.
 // Measured on MI355X (LTimes / LPlusTimes, D = 128, NM = 64, us, weights through LDS against this):
 // 2,000 columns 14 / 14 against 5.2 / 4.5; 8,000: 15 / 15 against 8.6 / 7.5; 16,384: 16 / 16 against
-// 13 / 12; 32,768: 18 / 20 against 26 / 26 (the weights are read once per 16 or 32 columns).
+// 13 / 12; 32,768: 18 / 20 against 26 / 26 (the weights are read once per 16 or 32 columns).  The line of
+// 16,384 columns is that shape's and taken for all D and NM; fewer weights would move it up.
 // 1 where the form is not taken, also where its registers would not fit.
 static int64_t cols_split(const SpecKey &k, bool *wdirect)
 {
@@ -422,7 +423,8 @@ sj_status make_key(sj_kernel k, const sj_spec *s, int device, const char *arch, 
 //   Q1D 7, 8: eight elements, 512 threads (D1D=5 Q1D=8 183 us against 345, D1D=6 Q1D=8 182 against 407)
 //   Q1D 9..14: one element, 128 threads (D1D=9 Q1D=9 217 us against 860, D1D=8 Q1D=12 201 against over 2000);
 //     wider elements need more threads for the registers (D1D=12 Q1D=12 257 us at 256, 821 at 128)
-//   Q1D <= 3 and 6: within 5% of the pipelined form, which stays (D1D=4 Q1D=6 187-200 us against 191-201)
+//   Q1D <= 3, and 6 as measured at D1D = 4, for every D1D: within 5% of the pipelined form, which stays
+//     (D1D=4 Q1D=6 187-200 us against 191-201)
 // Fewer elements per workgroup where the mesh would give less than two workgroups a CU.
 static bool mass_hex_tile(int64_t D, int64_t Q, int64_t ne, int *ew, int *block)
 {
