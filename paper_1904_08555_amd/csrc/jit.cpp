@@ -430,7 +430,9 @@ static bool mass_hex_tile(int64_t D, int64_t Q, int64_t ne, int *ew, int *block)
 {
     if (Q < 4 || Q == 6) return false;
     int e = Q <= 8 ? 8 : 1, b = Q <= 5 ? 256 : Q <= 8 ? 512 : std::max(D, Q) >= 17 ? 512 : (D >= 10 || Q >= 15) ? 256 : 128;
-    // a thread's x, y and point values in flight, and the LDS of a workgroup
+    // a thread's x, y and point values in flight, and the LDS of a workgroup.  (At 192 such values, D1D = Q1D = 8
+    // with eight elements by 64 threads, clang 20's code, which moves vectors of spilled scalars to the accumulator
+    // registers, gave wrong values for 24 elements and right ones for 20,001; clang 22's was right.  56 leaves room.)
     auto fits = [&] {
         const int64_t nx = (e * D * D * D + b - 1) / b, nz = (e * Q * Q + b - 1) / b;
         const int64_t lds = e * (std::max(D * D * (D | 1), D * Q * Q) + D * D * (Q | 1)) * 8;
