@@ -47,27 +47,101 @@ LAYOUTS = ("DGZ", "DZG", "GDZ", "GZD", "ZDG", "ZGD")
 # were taken on: a kernel whose source has changed since reports traffic null.  The summaries with the
 # commands are the trace-and-counter files of each workload under profiles/.
 MEASURED_TRAFFIC = {
-    # Z=32768 G=32 D=96 NM=16, the tuned specializations of the six nestings:
-    "a72057a4a6e7a246a15903f0c958be7b7c6b376f": 940050043,  # sj_lplustimes_cols_mfma_zdg
-    "2c7c9cdf86d4b19798fa6c15aa02847f433fd9de": 940673269,  # sj_lplustimes_direct_dgz
-    "d29a392ebc2ce6e725c4dc61fcb1f8aa2e82d8b6": 940707834,  # sj_lplustimes_direct_dzg
-    "65f93956b48e02a337a9396696699e9e7050d2e6": 940395639,  # sj_lplustimes_direct_gdz
-    "6faf012bc4aa3239ccf5492f1f96d8dbd3205c72": 939731581,  # sj_lplustimes_rows_mfma_gzd
-    "e92572674af57126b26f9a13a65126eeecfa5e3b": 939731197,  # sj_lplustimes_rows_mfma_zgd
-    "aac6be0336c61377439e3d3e3634416ed9e6bae9": 939763195,  # sj_ltimes_direct_dgz
-    "eab71f4174303315d32d91274d4ae3998ebd0aa5": 939762427,  # sj_ltimes_direct_dzg
-    "11390ff2859129b666d598b3a0cfb489186094d5": 939998966,  # sj_ltimes_direct_gdz
-    "75437275afe268eedc0d9369dd743e8d3ff4a576": 939734395,  # sj_ltimes_direct_zdg
-    "b780dade1ba9509a8d304488318c03b07830cce1": 939694844,  # sj_ltimes_rows_mfma_lds_gzd
-    "2c35009ddb2bddd0e9acd536270cc3e2c19c0777": 939694844,  # sj_ltimes_rows_mfma_lds_zgd
-    # other winners of the tuning on other boxes:
-    "096450941075a7b535ec0acdc4803e93fa480056": 940753013,  # sj_lplustimes_direct_dzg
-    "5eefde36174a8c0697380a33840eb250c860eea7": 940605045,  # sj_lplustimes_direct_gdz
-    "174c646463597e8495bac025d0588a78b135b42c": 939996918,  # sj_ltimes_direct_dgz
-    "6c19c99e0e177b5af870248564a960d78c9da2a4": 939996278,  # sj_ltimes_direct_dzg
+    # Z=32768 G=32 D=96 NM=16, the default specializations of the six nestings:
+    "e5177131244fdeb43d60b974b8abb2453c4c33a0": 939780480,  # sj_ltimes_direct_dgz
+    "6e1c7f526f3c2c86afea9bfc197b477b2f347bff": 940825472,  # sj_lplustimes_direct_dgz
+    "de8939ab33ab816e44aee56d6f0bed74d677b549": 939781120,  # sj_ltimes_direct_dzg
+    "debf32bc63a21fe902b7dc32df36718e6e47532d": 940684416,  # sj_lplustimes_direct_dzg
+    "5d6fc7e89ab323a27d8e9ef0178544c3fc44b090": 939777408,  # sj_ltimes_direct_gdz
+    "aee997d9ce8484d2af4a6a6c004db7f20ae5463d": 940489856,  # sj_lplustimes_direct_gdz
+    "88923bb0a0ee7d7b71dcd4ed3655fb222f0c118d": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "3e35e46e4c93cdcd4cf0f1480af061dd47ee8644": 939692032,  # sj_lplustimes_rows_mfma_lds_gzd
+    "c5f0d154bde02147eaea4fc9f1a912b6e1d179e7": 939776896,  # sj_ltimes_direct_zdg
+    "9e6c539d2629a7236a53de8f20434d0ddf324b0c": 940731136,  # sj_lplustimes_direct_zdg
+    "0398da146304969e311dc0dc1382810c8be1a795": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "2a522cb480be4657260111c1f671b576498be90f": 939697024,  # sj_lplustimes_rows_mfma_lds_zgd
+    # two tuned sets of them:
+    "a4d8549d5850b7c517e074df9ca57b1921c71b74": 939751936,  # sj_ltimes_direct_dgz
+    "ff750e67d3b87fb9e8bb9a813f95c54dab524182": 940547456,  # sj_lplustimes_direct_dgz
+    "28206668d130002c6c682f6eb99dde5843c9cf5d": 939752064,  # sj_ltimes_direct_dzg
+    "cbb210240cbf82f54e00cfca27fe2887cb2023c6": 940671488,  # sj_lplustimes_direct_dzg
+    "6f476037adec9939c45d825aef297493887602cd": 939754496,  # sj_ltimes_direct_gdz
+    "b8eea7944f32a81f187cea5353f3c1a08fae91f4": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "6faf012bc4aa3239ccf5492f1f96d8dbd3205c72": 939751680,  # sj_lplustimes_rows_mfma_gzd
+    "f4594008de9790ee2d4c19e48c4290524a19a3d3": 939750656,  # sj_ltimes_direct_zdg
+    "226cabe1aa695d94ff910fe1c5fb2669659a02d3": 939917440,  # sj_lplustimes_cols_mfma_zdg
+    "0d11f9b19c61e9871e95e206ab1bf56b075409f4": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "81dc44c3d6b6585eb218311c46e6bbc0b179cf1f": 940544256,  # sj_lplustimes_direct_dgz
+    "d7d8f5138e8dd8bd326d31bf32102eb855d7cbff": 939753472,  # sj_ltimes_direct_gdz
+    "75e98f9dd8d1121bc8b489ca0524dca2e808b5f8": 940505472,  # sj_lplustimes_direct_gdz
+    "c0e16a835bc83572ecf8ad42ec0fff4e713bdf37": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "06fbf2e445a7815ac5969c75782336bbd0793059": 939753600,  # sj_ltimes_direct_zdg
+    "428fb3b7dbc5a50022dea8284f025bdabaa27aa5": 940320256,  # sj_lplustimes_direct_zdg
+    "e491112c44defc6d807620484c1dc607339272bb": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "c9ee1470bfb94602eb0ea22725114c770abea167": 940003712,  # sj_lplustimes_rows_mfma_zgd
+    # LTimes on the LDS-staged row kernel, every tile, load, store and XCD form that tuning and the
+    # in-step refinement choose among:
+    "26ce55279febde4c323d0f124a2815c892c3847b": 939979520,  # sj_ltimes_rows_mfma_lds_gzd
+    "59301139cc6584d8dd46a2d7ea9c480dadf77f83": 939986560,  # sj_ltimes_rows_mfma_lds_gzd
+    "f3e0f1901372f3166c5748b4072d3519e4ef3867": 939941888,  # sj_ltimes_rows_mfma_lds_gzd
+    "b6487fac4f04191d6573edb13a932b2723e6d799": 939960832,  # sj_ltimes_rows_mfma_lds_gzd
+    "253de23d5dd51fd5802605844d5296b2c90639c7": 939698560,  # sj_ltimes_rows_mfma_lds_gzd
+    "df105d2d226f44357475cd18c6e6c93d0bbe118a": 939705600,  # sj_ltimes_rows_mfma_lds_gzd
+    "1c423f11e7d860df5c7782dd14f5adb9fb0fba8d": 939696896,  # sj_ltimes_rows_mfma_lds_gzd
+    "53917d9c28591c9762b0e82d1843355c68b39754": 939709696,  # sj_ltimes_rows_mfma_lds_gzd
+    "ca9678d37d72a0cec91e082cde5190c6165b6547": 939712640,  # sj_ltimes_rows_mfma_lds_gzd
+    "141de8046d75c80f62842a2cba08f0cc835e79c1": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "e55fcfaac7a661ee3a257e18692cd5fb485043b3": 939714944,  # sj_ltimes_rows_mfma_lds_gzd
+    "2c7297c4b4c6a50532b6cde3e5bf78f62eca2055": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "613b8b57287ffbe91938a7b18fb7bce6e4e026bf": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "c4c9021c4ea633ca9466d4374d11c4f60b82c37f": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "7b9fe413b59b4946815af5fe62713ad4b5358fb0": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "8a8e9a8e5707f404794eb7fb3bf40b33cc5b8967": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "6241e0c70e6ea4b04f2e924401da04253ba02575": 939677696,  # sj_ltimes_rows_mfma_lds_gzd
+    "ac94dd67d0e3aee32791cdaf4e4e9412cc4aef90": 939776000,  # sj_ltimes_rows_mfma_lds_gzd
+    "4207226ce442d8421e6b06a8bf4c337e60fe5611": 939678720,  # sj_ltimes_rows_mfma_lds_gzd
+    "ceb9d84a15218103fd92294bdd3ab8bfdb00e720": 939777024,  # sj_ltimes_rows_mfma_lds_gzd
+    "05277b6fe4c18d28710a4f626e45cd642b0ec3d5": 939679872,  # sj_ltimes_rows_mfma_lds_gzd
+    "95bd36f1d840ed8e70aa11143c6b0b310d25a927": 939679744,  # sj_ltimes_rows_mfma_lds_gzd
+    "b9503bdba0a123c7a1ba9349f8daa6b34ed57e3f": 939680768,  # sj_ltimes_rows_mfma_lds_gzd
+    "1f5b573e79be093321de0eeabee524fa6621a841": 939680768,  # sj_ltimes_rows_mfma_lds_gzd
+    "e0083a0d6eef9286c998d85a1da70e9ba37ce28b": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "5e61a2cc38ec69c8d4a87e250ed92c2f9a4269d5": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "a08ae19023b84585bd93ef5abb4cdd939dd25ea6": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "ff8fc4113c30cfe0548df65d53ee5342522699e3": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "3c581bf17fc63a61fec46b84f0c74b9cb70b5ff4": 939712512,  # sj_ltimes_rows_mfma_lds_gzd
+    "83605dbaff288f49bf3a342e3f4391f29a01a5d4": 939950720,  # sj_ltimes_rows_mfma_lds_zgd
+    "009e73b97ca5be95efd5f1e4f4c53760135d85f1": 939999744,  # sj_ltimes_rows_mfma_lds_zgd
+    "23b167a320b50a3b3569934af43da28bcfdd017a": 939956224,  # sj_ltimes_rows_mfma_lds_zgd
+    "21b9415cf2323d347ec6b65eb939715758895546": 939976192,  # sj_ltimes_rows_mfma_lds_zgd
+    "306f2bf719d52825c446b78cd269b37f4bc935cf": 939715456,  # sj_ltimes_rows_mfma_lds_zgd
+    "55bd626790bb14981549940d8908c0a8f80e0495": 939717120,  # sj_ltimes_rows_mfma_lds_zgd
+    "9a56a463b679c47ad1f053d2a0d34127ef22e48f": 939689728,  # sj_ltimes_rows_mfma_lds_zgd
+    "82a558cf88273aa619c53e9a85f800fd8bda18fa": 939697024,  # sj_ltimes_rows_mfma_lds_zgd
+    "0eda916a7a7c56c8a738696168ad06c8c259c764": 939713280,  # sj_ltimes_rows_mfma_lds_zgd
+    "70eb8fa7d8d974499964858ea0dfb41065df9705": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "9781daf35ba5e66b11b8b339703e626608d3a903": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "89b46baed9beeb539d8573b34a340d8bc5ea216c": 939713792,  # sj_ltimes_rows_mfma_lds_zgd
+    "89ba20b89a20045c6960d20360e103e643a2ee28": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "9dfd3b1d9cc9a9876bee7ae4421dc03f1982c620": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "0255efe9ab92dcea2ba9782907f84d8a7de3e3ab": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "91961e3317b0876b009bda1e79fb6efe9695ec87": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "ffe28a1f34110255e99f40d936e5086c8b08daae": 939677696,  # sj_ltimes_rows_mfma_lds_zgd
+    "28f02bae3762893500399aca33248d60b1c411b8": 939776128,  # sj_ltimes_rows_mfma_lds_zgd
+    "b47e48b1e85f042abb53e4b3a09a490c7c97903d": 939678720,  # sj_ltimes_rows_mfma_lds_zgd
+    "960d96ed3450536c121f429afba54ddd534e59bc": 939777024,  # sj_ltimes_rows_mfma_lds_zgd
+    "963b8e7b0a3f5a6ad47f6a3d8124b26d81b3a76a": 939679744,  # sj_ltimes_rows_mfma_lds_zgd
+    "ea13803c561a3faa1d84e424a22f247797dcaf25": 939679744,  # sj_ltimes_rows_mfma_lds_zgd
+    "2df1a931503ca712f4234fadee5911591efefd0c": 939680768,  # sj_ltimes_rows_mfma_lds_zgd
+    "e7f259b93d2f758ef2a20661a7cecd54b24f7f36": 939680896,  # sj_ltimes_rows_mfma_lds_zgd
+    "ffb148281577ef39372e09272a72f32011cb6bea": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "24db07d264a314b800237d9eab7f97e31578254a": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "4bda90badba9cbe73192ec20d44a0c603f5803b6": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "7e836639441e63d40e4f8bc65711296f0c4fe750": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
+    "f0bf89cb34e6aeb313e2954286a5d862dcb480a5": 939712512,  # sj_ltimes_rows_mfma_lds_zgd
     # scattering (4 materials in zone regions, Z=32768 G=32 NM=16), default specializations:
     "5b273898027180bb79c395b49cf8c70e35f9030d": 270032989,  # sj_scattering_direct_gzd
-    "f0a893edca371ae328b11107c4a596cd243f06c2": 270058588,  # sj_scattering_direct_zgd
+    "3166aed504c9b5536fc58aa6ef894470ab347351": 269947008,  # sj_scattering_direct_zgd (zones sorted by material)
     "72b818d409165b1caf6e7b882fec2e1d87c7090f": 269172848,  # sj_scattering_mfma_dgz
     "3b3f5766b2cce9423127a1ac1c61af4316f5e8a1": 270377301,  # sj_scattering_mfma_dzg
     "fa7a996b5cbceafbf17b0ee3785a13d0807319f2": 269172848,  # sj_scattering_mfma_gdz
@@ -91,17 +165,9 @@ MEASURED_TRAFFIC = {
     "11d9a11b89c49eb5977c1f64152ffa1996085ad5": 12885495542,  # sj_ltimes_bf16x3w_dgz
     # batched products, 200,000 instances n ~ U{3..16}, default specialization:
     "c3ba1c297bdc9d6ccad6fbee12c99a6e3f992468": 533975253,  # sj_bgemm_persistent
-    # Z=32768 G=32 D=96 NM=16, another tuned set of the six nestings (the LDS-staged row LTimes with
-    # two row tiles per wave, rotation and workgroups on contiguous XCD ranges):
-    "caf4ba83110b0c9b595ccea83e82d168fa284f15": 940723317,  # sj_lplustimes_direct_dgz (read 134.7 MB, written 806.0 MB)
-    "b5f2c3a8fd909fd198ad33fa9fcc6bf107e645fa": 940802293,  # sj_lplustimes_direct_dzg (read 134.7 MB, written 806.1 MB)
-    "17fd69e3b29440e0f912deb3add2f6c1d8336777": 940737525,  # sj_lplustimes_direct_gdz (read 134.7 MB, written 806.0 MB)
-    "57160d60ee27647a4376d637645887fbcdf2dc84": 940342136,  # sj_lplustimes_direct_zdg (read 134.6 MB, written 805.8 MB)
-    "c9ee1470bfb94602eb0ea22725114c770abea167": 939964157,  # sj_lplustimes_rows_mfma_zgd (read 134.3 MB, written 805.6 MB)
-    "4536cc7cb047bfe2cc8fe4196b61564ef4249a63": 939732731,  # sj_ltimes_direct_dgz (read 805.5 MB, written 134.2 MB)
-    "133d138961c05fb37623878b4f19d58e5f256ae1": 939995126,  # sj_ltimes_direct_dzg (read 805.8 MB, written 134.2 MB)
-    "f9e011450da5ffd5c729f1fc92560b93116f25d1": 939694844,  # sj_ltimes_rows_mfma_lds_gzd (read 805.5 MB, written 134.2 MB)
-    "39f562d0cb6361bc8681a427185ee496c7bbf708": 939694844,  # sj_ltimes_rows_mfma_lds_zgd (read 805.5 MB, written 134.2 MB)
+    # Z=4096 G=8 D=48 NM=16, the default specializations:
+    "90311e8298ecd1e5dbbbc18c20178d805487d9d3": 16851968,  # sj_ltimes_cols_mfma_dgz
+    "c62f631623422a2852822ea8c615bb2a3099d507": 16851968,  # sj_lplustimes_cols_mfma_dgz
 }
 
 
@@ -109,16 +175,76 @@ MEASURED_TRAFFIC = {
 # x 1024 SIMDs), keyed like MEASURED_TRAFFIC; the summary with the commands is
 # profiles/mfma_busy_moments_bf16_bgemm_counters.md.
 MEASURED_MFMA_BUSY = {
-    # Z=32768 G=32 D=96 NM=16 (FP64 matrix cores)
-    "a72057a4a6e7a246a15903f0c958be7b7c6b376f": 0.219,  # sj_lplustimes_cols_mfma_zdg
-    "6faf012bc4aa3239ccf5492f1f96d8dbd3205c72": 0.181,  # sj_lplustimes_rows_mfma_gzd
-    "e92572674af57126b26f9a13a65126eeecfa5e3b": 0.182,  # sj_lplustimes_rows_mfma_zgd
-    "b780dade1ba9509a8d304488318c03b07830cce1": 0.261,  # sj_ltimes_rows_mfma_lds_gzd
-    "2c35009ddb2bddd0e9acd536270cc3e2c19c0777": 0.260,  # sj_ltimes_rows_mfma_lds_zgd
-    # the same shape, the second tuned set (two row tiles per wave, rotation, contiguous XCD ranges)
-    "f9e011450da5ffd5c729f1fc92560b93116f25d1": 0.262,  # sj_ltimes_rows_mfma_lds_gzd
-    "39f562d0cb6361bc8681a427185ee496c7bbf708": 0.259,  # sj_ltimes_rows_mfma_lds_zgd
-    "c9ee1470bfb94602eb0ea22725114c770abea167": 0.222,  # sj_lplustimes_rows_mfma_zgd
+    # Z=32768 G=32 D=96 NM=16 (FP64 matrix cores), in the step
+    "88923bb0a0ee7d7b71dcd4ed3655fb222f0c118d": 0.250,  # sj_ltimes_rows_mfma_lds_gzd
+    "3e35e46e4c93cdcd4cf0f1480af061dd47ee8644": 0.226,  # sj_lplustimes_rows_mfma_lds_gzd
+    "0398da146304969e311dc0dc1382810c8be1a795": 0.253,  # sj_ltimes_rows_mfma_lds_zgd
+    "2a522cb480be4657260111c1f671b576498be90f": 0.226,  # sj_lplustimes_rows_mfma_lds_zgd
+    "b8eea7944f32a81f187cea5353f3c1a08fae91f4": 0.264,  # sj_ltimes_rows_mfma_lds_gzd
+    "6faf012bc4aa3239ccf5492f1f96d8dbd3205c72": 0.183,  # sj_lplustimes_rows_mfma_gzd
+    "226cabe1aa695d94ff910fe1c5fb2669659a02d3": 0.224,  # sj_lplustimes_cols_mfma_zdg
+    "0d11f9b19c61e9871e95e206ab1bf56b075409f4": 0.263,  # sj_ltimes_rows_mfma_lds_zgd
+    # the LDS-staged row LTimes in every form, each launch after a 1 GiB read and write
+    "26ce55279febde4c323d0f124a2815c892c3847b": 0.173,  # sj_ltimes_rows_mfma_lds_gzd
+    "59301139cc6584d8dd46a2d7ea9c480dadf77f83": 0.175,  # sj_ltimes_rows_mfma_lds_gzd
+    "f3e0f1901372f3166c5748b4072d3519e4ef3867": 0.169,  # sj_ltimes_rows_mfma_lds_gzd
+    "b6487fac4f04191d6573edb13a932b2723e6d799": 0.172,  # sj_ltimes_rows_mfma_lds_gzd
+    "253de23d5dd51fd5802605844d5296b2c90639c7": 0.183,  # sj_ltimes_rows_mfma_lds_gzd
+    "df105d2d226f44357475cd18c6e6c93d0bbe118a": 0.187,  # sj_ltimes_rows_mfma_lds_gzd
+    "1c423f11e7d860df5c7782dd14f5adb9fb0fba8d": 0.178,  # sj_ltimes_rows_mfma_lds_gzd
+    "53917d9c28591c9762b0e82d1843355c68b39754": 0.183,  # sj_ltimes_rows_mfma_lds_gzd
+    "ca9678d37d72a0cec91e082cde5190c6165b6547": 0.179,  # sj_ltimes_rows_mfma_lds_gzd
+    "141de8046d75c80f62842a2cba08f0cc835e79c1": 0.183,  # sj_ltimes_rows_mfma_lds_gzd
+    "e55fcfaac7a661ee3a257e18692cd5fb485043b3": 0.181,  # sj_ltimes_rows_mfma_lds_gzd
+    "2c7297c4b4c6a50532b6cde3e5bf78f62eca2055": 0.183,  # sj_ltimes_rows_mfma_lds_gzd
+    "613b8b57287ffbe91938a7b18fb7bce6e4e026bf": 0.186,  # sj_ltimes_rows_mfma_lds_gzd
+    "c4c9021c4ea633ca9466d4374d11c4f60b82c37f": 0.194,  # sj_ltimes_rows_mfma_lds_gzd
+    "7b9fe413b59b4946815af5fe62713ad4b5358fb0": 0.189,  # sj_ltimes_rows_mfma_lds_gzd
+    "8a8e9a8e5707f404794eb7fb3bf40b33cc5b8967": 0.195,  # sj_ltimes_rows_mfma_lds_gzd
+    "6241e0c70e6ea4b04f2e924401da04253ba02575": 0.216,  # sj_ltimes_rows_mfma_lds_gzd
+    "ac94dd67d0e3aee32791cdaf4e4e9412cc4aef90": 0.205,  # sj_ltimes_rows_mfma_lds_gzd
+    "4207226ce442d8421e6b06a8bf4c337e60fe5611": 0.214,  # sj_ltimes_rows_mfma_lds_gzd
+    "ceb9d84a15218103fd92294bdd3ab8bfdb00e720": 0.204,  # sj_ltimes_rows_mfma_lds_gzd
+    "05277b6fe4c18d28710a4f626e45cd642b0ec3d5": 0.241,  # sj_ltimes_rows_mfma_lds_gzd
+    "95bd36f1d840ed8e70aa11143c6b0b310d25a927": 0.228,  # sj_ltimes_rows_mfma_lds_gzd
+    "b9503bdba0a123c7a1ba9349f8daa6b34ed57e3f": 0.229,  # sj_ltimes_rows_mfma_lds_gzd
+    "1f5b573e79be093321de0eeabee524fa6621a841": 0.221,  # sj_ltimes_rows_mfma_lds_gzd
+    "e0083a0d6eef9286c998d85a1da70e9ba37ce28b": 0.234,  # sj_ltimes_rows_mfma_lds_gzd
+    "5e61a2cc38ec69c8d4a87e250ed92c2f9a4269d5": 0.224,  # sj_ltimes_rows_mfma_lds_gzd
+    "a08ae19023b84585bd93ef5abb4cdd939dd25ea6": 0.237,  # sj_ltimes_rows_mfma_lds_gzd
+    "ff8fc4113c30cfe0548df65d53ee5342522699e3": 0.212,  # sj_ltimes_rows_mfma_lds_gzd
+    "c0e16a835bc83572ecf8ad42ec0fff4e713bdf37": 0.239,  # sj_ltimes_rows_mfma_lds_gzd
+    "3c581bf17fc63a61fec46b84f0c74b9cb70b5ff4": 0.264,  # sj_ltimes_rows_mfma_lds_gzd
+    "83605dbaff288f49bf3a342e3f4391f29a01a5d4": 0.170,  # sj_ltimes_rows_mfma_lds_zgd
+    "009e73b97ca5be95efd5f1e4f4c53760135d85f1": 0.174,  # sj_ltimes_rows_mfma_lds_zgd
+    "23b167a320b50a3b3569934af43da28bcfdd017a": 0.170,  # sj_ltimes_rows_mfma_lds_zgd
+    "21b9415cf2323d347ec6b65eb939715758895546": 0.172,  # sj_ltimes_rows_mfma_lds_zgd
+    "306f2bf719d52825c446b78cd269b37f4bc935cf": 0.185,  # sj_ltimes_rows_mfma_lds_zgd
+    "55bd626790bb14981549940d8908c0a8f80e0495": 0.190,  # sj_ltimes_rows_mfma_lds_zgd
+    "9a56a463b679c47ad1f053d2a0d34127ef22e48f": 0.179,  # sj_ltimes_rows_mfma_lds_zgd
+    "82a558cf88273aa619c53e9a85f800fd8bda18fa": 0.185,  # sj_ltimes_rows_mfma_lds_zgd
+    "0eda916a7a7c56c8a738696168ad06c8c259c764": 0.178,  # sj_ltimes_rows_mfma_lds_zgd
+    "70eb8fa7d8d974499964858ea0dfb41065df9705": 0.182,  # sj_ltimes_rows_mfma_lds_zgd
+    "9781daf35ba5e66b11b8b339703e626608d3a903": 0.181,  # sj_ltimes_rows_mfma_lds_zgd
+    "89b46baed9beeb539d8573b34a340d8bc5ea216c": 0.182,  # sj_ltimes_rows_mfma_lds_zgd
+    "89ba20b89a20045c6960d20360e103e643a2ee28": 0.189,  # sj_ltimes_rows_mfma_lds_zgd
+    "9dfd3b1d9cc9a9876bee7ae4421dc03f1982c620": 0.194,  # sj_ltimes_rows_mfma_lds_zgd
+    "0255efe9ab92dcea2ba9782907f84d8a7de3e3ab": 0.195,  # sj_ltimes_rows_mfma_lds_zgd
+    "91961e3317b0876b009bda1e79fb6efe9695ec87": 0.197,  # sj_ltimes_rows_mfma_lds_zgd
+    "ffe28a1f34110255e99f40d936e5086c8b08daae": 0.215,  # sj_ltimes_rows_mfma_lds_zgd
+    "28f02bae3762893500399aca33248d60b1c411b8": 0.205,  # sj_ltimes_rows_mfma_lds_zgd
+    "b47e48b1e85f042abb53e4b3a09a490c7c97903d": 0.213,  # sj_ltimes_rows_mfma_lds_zgd
+    "960d96ed3450536c121f429afba54ddd534e59bc": 0.208,  # sj_ltimes_rows_mfma_lds_zgd
+    "963b8e7b0a3f5a6ad47f6a3d8124b26d81b3a76a": 0.233,  # sj_ltimes_rows_mfma_lds_zgd
+    "ea13803c561a3faa1d84e424a22f247797dcaf25": 0.229,  # sj_ltimes_rows_mfma_lds_zgd
+    "2df1a931503ca712f4234fadee5911591efefd0c": 0.232,  # sj_ltimes_rows_mfma_lds_zgd
+    "e7f259b93d2f758ef2a20661a7cecd54b24f7f36": 0.219,  # sj_ltimes_rows_mfma_lds_zgd
+    "ffb148281577ef39372e09272a72f32011cb6bea": 0.240,  # sj_ltimes_rows_mfma_lds_zgd
+    "24db07d264a314b800237d9eab7f97e31578254a": 0.222,  # sj_ltimes_rows_mfma_lds_zgd
+    "4bda90badba9cbe73192ec20d44a0c603f5803b6": 0.238,  # sj_ltimes_rows_mfma_lds_zgd
+    "7e836639441e63d40e4f8bc65711296f0c4fe750": 0.221,  # sj_ltimes_rows_mfma_lds_zgd
+    "e491112c44defc6d807620484c1dc607339272bb": 0.236,  # sj_ltimes_rows_mfma_lds_zgd
+    "f0bf89cb34e6aeb313e2954286a5d862dcb480a5": 0.254,  # sj_ltimes_rows_mfma_lds_zgd
     # Z=262144 G=64 D=128 NM=64: FP64 column kernel, BF16 forms
     "1d98ee3ef25cf25ec41313284a3c5dd1789a6681": 0.037,  # sj_ltimes_bf16_dgz
     "111efaeca57317b4febbd7e1e0bcd93abbe5ee20": 0.047,  # sj_ltimes_bf16_rows_zgd
@@ -126,7 +252,7 @@ MEASURED_MFMA_BUSY = {
     "064caca9d342bd247e528f7049d4fd9123058c51": 0.129,  # sj_ltimes_bf16x3_dgz
     "02608d4c7c058928c9748fb885a634bc6dbe4165": 0.162,  # sj_ltimes_bf16x3_rows_zgd
     "11d9a11b89c49eb5977c1f64152ffa1996085ad5": 0.175,  # sj_ltimes_bf16x3w_dgz
-    "60467b2e08b71a9f23cd2cf2872db0e82932347b": 0.766,  # sj_ltimes_cols_mfma_dgz
+    "74e5832ac4b1874fec2036a8cb5bdaa78b434319": 0.760,  # sj_ltimes_cols_mfma_dgz
     # batched products, 200,000 instances n ~ U{3..16}
     "c3ba1c297bdc9d6ccad6fbee12c99a6e3f992468": 0.169,  # sj_bgemm_persistent
 }
