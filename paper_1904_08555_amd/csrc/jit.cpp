@@ -279,8 +279,8 @@ static int64_t scattering_sorted_moments(const SpecKey &k)
 // multiple of a 128-byte line move the line down (65,535 columns 25 / 18 against 20 / 18), few moments too
 // (NM = 4, D = 48, 65,536 columns: 6.5 / 5.9 against 6.6 / 5.9).  Very short rows (ZDG with up to 8 groups)
 // take the matrix cores at any size: a quarter-wave covers 16 columns whatever record they are in
-// (62,035 zones of 2 groups, D = 27, NM = 9: 12 / 14 against 8.4 / 9.6).  Chains of up to 256 products
-// are done within a launch's time either way.
+// (62,035 zones of 2 groups, D = 27, NM = 9: 12 / 14 against 8.4 / 9.6; 300,000 zones of 5, D = 72, NM = 9:
+// 201 / 311 against 206 / 196).  Chains of up to 256 products are done within a launch's time either way.
 static bool cols_mfma_tile(const sj_spec *s, bool ltimes, int64_t B, int64_t I, sj_spec *mf)
 {
     if (I <= 1 || s->tile_n || s->tile_k || s->unroll || s->block || s->order) return false;
@@ -1142,7 +1142,17 @@ Geometry key_geometry(const SpecKey &k)
         } else if (cols_mfma(k)) {
             bool wdirect = false;
             const int64_t items = cols_tiles(k) * cols_split(k, &wdirect), waves = k.block / 64;
-            g.grid = (unsigned)std::min<int64_t>((items + waves - 1) / waves, 2048);
+            // every wave as many tiles as the others: capped at 2048 workgroups, 300,000 columns left most of a
+            // second round empty (LTimes / LPlusTimes, us, capped against this: ZDG 60,000 x 5 D=72 NM=9 45 / 57
+            // against 33 / 37, DGZ 300,000 D=128 NM=64 183 / 190 against 134 / 144).  Up to 32 weight fragments
+            // one tile a wave, more in rounds of at most 2048 workgroups, which load the weights less often
+            // (1,500,000 columns, I = 2: LPlusTimes D=96 NM=16, 24 fragments, 345 with one tile a wave, 386 in
+            // rounds; LTimes D=72 NM=36, 54 fragments, 374, 329; nothing was measured between 24 and 45).
+            const bool lt = k.kernel == SJ_LTIMES;
+            const int64_t frags = (((lt ? k.D : k.NM) + 3) / 4) * (((lt ? k.NM : k.D) + 15) / 16);
+            const int64_t blocks = (items + waves - 1) / waves, most = frags <= 32 ? 1 << 20 : 2048;
+            const int64_t rounds = (blocks + most - 1) / most;
+            g.grid = (unsigned)((blocks + rounds - 1) / rounds);
         } else if (k.variant == SJ_VAR_MFMA && k.dtype == SJ_F64 && k.kernel == SJ_LTIMES_LPLUS) {
             // persistent: at most one group of tiles per wave; capped at load time to the
             // workgroups the device holds at once

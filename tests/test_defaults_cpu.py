@@ -197,3 +197,14 @@ def test_features_of_few_rows():
 def test_stores_of_long_rows(layout, Z, G, D, NM, stores):
     flags = P.sj_resolve(P.SJ_LPLUSTIMES, layout=layout, Z=Z, G=G, D=D, NM=NM)["flags"]
     assert flags & getattr(P, "SJ_FLAG_STORES_" + stores) and flags & P.SJ_FLAG_LOADS_CACHED
+
+
+# the column kernel's workgroups: one tile a wave where the weights are few, else rounds of at most 2048 that
+# are all full, and never a launch of 2^32 threads
+@pytest.mark.parametrize("kernel,layout,Z,G,D,NM,grid", [
+    ("SJ_LPLUSTIMES", "ZDG", 60000, 5, 72, 9, 2344), ("SJ_LTIMES", "ZDG", 150000, 2, 72, 9, 2344), ("SJ_LTIMES", "DGZ", 300000, 1, 128, 64, 1172),
+    ("SJ_LPLUSTIMES", "DGZ", 262144, 1, 128, 64, 2048), ("SJ_LTIMES", "ZDG", 750000, 2, 72, 36, 1954), ("SJ_LPLUSTIMES", "ZDG", 400000000, 5, 1, 1, 1041667)])
+def test_column_rounds(kernel, layout, Z, G, D, NM, grid):
+    h = P.sj_specialize(getattr(P, kernel), layout=layout, Z=Z, G=G, D=D, NM=NM, flags=P.SJ_FLAG_COMPILE_ONLY)
+    info = P.sj_handle_info(h)
+    assert "cols_mfma" in info["kernel_name"] and info["grid"] == grid and grid * info["block"] < 2 ** 32

@@ -69,6 +69,15 @@ def test_column_forms(P, orc, layout, Z, G, D, NM, wdirect, split, flat, tile, b
         contraction(P, orc, k, layout, Z, G, D, NM, accumulate, spec)
 
 
+# more tiles than 2048 workgroups hold at once: one tile a wave, and full rounds with a ragged last tile
+@pytest.mark.parametrize("layout,Z,G,D,NM", [("ZDG", 53001, 5, 17, 4), ("ZDG", 140003, 2, 8, 3), ("DGZ", 270016, 1, 33, 64), ("ZDG", 135001, 2, 72, 33)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_column_rounds(P, orc, layout, Z, G, D, NM, accumulate):
+    for k in (P.SJ_LTIMES, P.SJ_LPLUSTIMES):
+        spec = dict(layout=layout, Z=Z, G=G, D=D, NM=NM, variant=P.SJ_VAR_MFMA, flags=P.SJ_FLAG_ACCUMULATE if accumulate else 0)
+        contraction(P, orc, k, layout, Z, G, D, NM, accumulate, spec)
+
+
 # accumulating rows: two tiles a wave, one, and operands read by the lanes; rows that end inside a group
 @pytest.mark.parametrize("Z,D,NM,tile,order", [(20003, 113, 25, 1, 2), (70001, 125, 16, 1, 2), (70001, 112, 25, 2, 2), (8203, 256, 36, 1, 1),
                                                (8195, 127, 64, 1, 2), (8200, 273, 16, 1, 1)])
