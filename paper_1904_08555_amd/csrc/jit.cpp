@@ -1277,11 +1277,9 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
     // GDZ rows of 8,671, D = 112, NM = 4 40.5 / 33.3; matrix cores, ZDG 1,387 x 47, D = 72, NM = 16 43 / 25),
     // but not where LPlusTimes writes longer rows that the caches hold (DGZ 46,341 columns, D = 112, NM = 4
     // 18.6 nontemporal, 24.8 ordinary), forms them from many moments (GDZ rows of 30,010, D = 96, NM = 25
-    // 158 / 198) or in 16-byte pieces, two columns a thread (even rows; pairs, NM = 16 GDZ rows of 54,366, D = 96
-    // 451 / 478, of 8,194 289 / 308, DGZ 1,000,008 columns 316 / 373, NM = 9 GDZ rows of 20,002, D = 64 285 / 307;
-    // odd rows of 54,365, D = 96, NM = 16 544 / 525, of 40,003, D = 120, NM = 9 415 / 390; NM = 4 GDZ rows of
-    // 16,998, D = 48 142 / 129; with nontemporal loads the last three take 541, 391 and 132) or, fused, after
-    // many moments (ZDG 4,100 x 30, D = 64, NM = 36 47 / 84; D = 96, NM = 16 54 / 50).  The matrix-core form reads ragged rows in 128-byte pieces: ordinary loads.
+    // 158 / 198) or in 16-byte pieces of middling rows (GDZ rows of 6,330, D = 80, NM = 16 97 / 109; of
+    // 30,882, D = 112 231 / 217) or, fused, after many moments (ZDG 4,100 x 30, D = 64, NM = 36 47 / 84; D = 96,
+    // NM = 16 54 / 50).  The matrix-core form reads ragged rows in 128-byte pieces: ordinary loads.
     // The fused matrix-core columns are few enough to stay in the caches: ordinary loads (DZG 25,485 columns,
     // D = 82, NM = 25 19.9 nontemporal, 14.5 ordinary; ZDG 1017 x 42, NM = 16 19.2 / 14.3), and stores where short
     // rows share lines (GDZ rows of 66, NM = 25 5.3 / 4.8).
@@ -1297,10 +1295,10 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
             if (lt && big) nts = 0;
             if (k.kernel == SJ_LPLUSTIMES && big && k.NM > 48) ntl = 1;
         } else {
-            const bool long_rows = k.I > 64 && k.NM <= 16 && k.B * k.I * k.D >= 10000000 && (k.I % 2 != 0 || k.NM < 9);
+            const bool long_rows = k.NM <= 16 && k.B * k.I * k.D >= 10000000 && (k.I % 2 != 0 || k.I >= 16384);
             if (lt || mfma || (k.I <= 64 && (k.kernel == SJ_LPLUSTIMES || k.NM <= 16)) || long_rows) nts = 0;
             if (lt && mfma) ntl = 0;
-            if (k.kernel == SJ_LPLUSTIMES) ntl = !nts && !long_rows;
+            if (k.kernel == SJ_LPLUSTIMES) ntl = !nts;
         }
     }
     if (k.flags & SJ_FLAG_LOADS_CACHED) ntl = 0;

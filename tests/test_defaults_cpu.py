@@ -188,17 +188,6 @@ def test_features_of_few_rows():
     assert (f[15], f[16]) == (0.0, 1.0)
 
 
-# LPlusTimes' stores of long rows that are no multiple of a line: nontemporal in 16-byte pieces (even rows),
-# ordinary value by value (odd rows) and from few moments; ordinary loads either way
-@pytest.mark.parametrize("layout,Z,G,D,NM,stores", [("GDZ", 54366, 23, 96, 16, "NONTEMPORAL"), ("GDZ", 54365, 23, 96, 16, "CACHED"),
-                                                    ("DGZ", 250002, 4, 96, 16, "NONTEMPORAL"), ("GDZ", 20002, 60, 64, 9, "NONTEMPORAL"),
-                                                    ("GDZ", 16998, 50, 48, 4, "CACHED"), ("GDZ", 8194, 100, 96, 16, "NONTEMPORAL"),
-                                                    ("GDZ", 60002, 12, 104, 25, "NONTEMPORAL")])
-def test_stores_of_long_rows(layout, Z, G, D, NM, stores):
-    flags = P.sj_resolve(P.SJ_LPLUSTIMES, layout=layout, Z=Z, G=G, D=D, NM=NM)["flags"]
-    assert flags & getattr(P, "SJ_FLAG_STORES_" + stores) and flags & P.SJ_FLAG_LOADS_CACHED
-
-
 # the column kernel's workgroups: one tile a wave where the weights are few, else rounds of at most 2048 that
 # are all full, and never a launch of 2^32 threads
 @pytest.mark.parametrize("kernel,layout,Z,G,D,NM,grid", [
