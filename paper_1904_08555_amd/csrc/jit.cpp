@@ -1279,7 +1279,10 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
     // 18.6 nontemporal, 24.8 ordinary), forms them from many moments (GDZ rows of 30,010, D = 96, NM = 25
     // 158 / 198) or in 16-byte pieces of middling rows (GDZ rows of 6,330, D = 80, NM = 16 97 / 109; of
     // 30,882, D = 112 231 / 217) or, fused, after many moments (ZDG 4,100 x 30, D = 64, NM = 36 47 / 84; D = 96,
-    // NM = 16 54 / 50).  The matrix-core form reads ragged rows in 128-byte pieces: ordinary loads.
+    // NM = 16 54 / 50), or where rows of 16,384 values on end in half a line and 512 MiB are written (GDZ rows
+    // of 54,360, a pair / fused, ordinary and these: 40 groups, D = 64, NM = 9 510 / 478 and 445 / 447, 25 groups
+    // 295 / 298 and 281 / 275; 9 groups 99 / 85 and 99 / 97; rows of 54,366, 25 groups 303 / 313 and 326 / 310).
+    // The matrix-core form reads ragged rows in 128-byte pieces: ordinary loads.
     // The fused matrix-core columns are few enough to stay in the caches: ordinary loads (DZG 25,485 columns,
     // D = 82, NM = 25 19.9 nontemporal, 14.5 ordinary; ZDG 1017 x 42, NM = 16 19.2 / 14.3), and stores where short
     // rows share lines (GDZ rows of 66, NM = 25 5.3 / 4.8).
@@ -1295,7 +1298,8 @@ void load_store_policy(const SpecKey &k, int *nt_load, int *nt_store)
             if (lt && big) nts = 0;
             if (k.kernel == SJ_LPLUSTIMES && big && k.NM > 48) ntl = 1;
         } else {
-            const bool long_rows = k.NM <= 16 && k.B * k.I * k.D >= 10000000 && (k.I % 2 != 0 || k.I >= 16384);
+            const bool half_lines = k.I % 16 == 8 && k.B * k.I * k.D > int64_t(1) << 26;
+            const bool long_rows = k.NM <= 16 && k.B * k.I * k.D >= 10000000 && (k.I % 2 != 0 || (k.I >= 16384 && !half_lines));
             if (lt || mfma || (k.I <= 64 && (k.kernel == SJ_LPLUSTIMES || k.NM <= 16)) || long_rows) nts = 0;
             if (lt && mfma) ntl = 0;
             if (k.kernel == SJ_LPLUSTIMES) ntl = !nts;

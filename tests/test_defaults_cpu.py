@@ -197,3 +197,13 @@ def test_column_rounds(kernel, layout, Z, G, D, NM, grid):
     h = P.sj_specialize(getattr(P, kernel), layout=layout, Z=Z, G=G, D=D, NM=NM, flags=P.SJ_FLAG_COMPILE_ONLY)
     info = P.sj_handle_info(h)
     assert "cols_mfma" in info["kernel_name"] and info["grid"] == grid and grid * info["block"] < 2 ** 32
+
+
+# even long rows: ordinary stores, but nontemporal ones where every other line of more than 512 MiB is cut in half
+@pytest.mark.parametrize("layout,Z,G,D,NM,stores", [("GDZ", 54360, 25, 64, 9, "NONTEMPORAL"), ("GDZ", 54360, 9, 64, 9, "CACHED"),
+                                                    ("GDZ", 54366, 40, 64, 9, "CACHED"), ("DGZ", 250002, 4, 96, 16, "NONTEMPORAL"),
+                                                    ("GDZ", 50002, 10, 64, 9, "CACHED"), ("GDZ", 54365, 40, 64, 9, "CACHED")])
+def test_stores_of_half_lines(layout, Z, G, D, NM, stores):
+    for kernel in (P.SJ_LPLUSTIMES, P.SJ_LTIMES_LPLUS):
+        flags = P.sj_resolve(kernel, layout=layout, Z=Z, G=G, D=D, NM=NM)["flags"]
+        assert flags & getattr(P, "SJ_FLAG_STORES_" + stores)
