@@ -223,6 +223,10 @@ static bool scattering_z_inner(int layout, int64_t G, int64_t NM)
 //     group's rows lie 64 KiB apart or a multiple of it keeps the thread per line: a block's runs
 //     of all groups fall on the same channels (Z=32768 G=32 NM=16 82/85 against 59/195, though
 //     only if the boundaries fall between waves).
+//     8 ... 10 groups fill about half of a tile's 16 outputs, so with many moments the thread per line
+//     is faster from about 150,000 lines on (zone order / drawn, sorted against it, times: ZGD G=8 NM=16
+//     Z=9857 0.99/1.32, Z=20001 1.67/1.24, Z=110000 1.66/1.14, NM=49 1.23 ... 1.79; G=9 NM=36 Z=5000
+//     1.09/1.43, NM=49 1.09 ... 1.61; but G=9 NM=16 Z=20001 1.07/0.79, G=8 NM=12 Z=70000 0.86/0.74).
 // Zones per block, nm innermost: two workgroups a CU (one below 16 zones), not so many that a
 // thread's values (20 doubles loaded one by one, or 36 in pairs) and their offsets fill its
 // registers (Z=9000 G=24 NM=25: 36/48 with 8 zones, 52/61 with 16), and a block for every CU
@@ -243,6 +247,7 @@ static bool scattering_sorted_tile(int layout, int64_t Z, int64_t G, int64_t NM,
         return z_inner && ((G >= 31 && (lines <= 131072 || Z % 16 != 0)) || (G > 16 && lines <= 32768));
     }
     if (NM > 64 || G < 8 || (layout == SJ_GZD && G <= 32 && Z * NM % 8192 == 0)) return false;
+    if (Z * NM >= 150000 && ((G == 8 && NM >= 16) || (G <= 10 && NM >= 36))) return false;
     const int64_t most = NM % 2 == 0 ? 36 : 20;   // a thread's values
     *block = G <= 32 ? 256 : 512;
     for (*zb = 64; *zb > 1 && *zb * scattering_sorted_zone(G, NM) * 8 > (*zb >= 16 ? 76 : 140) * 1024;) *zb /= 2;

@@ -207,3 +207,12 @@ def test_stores_of_half_lines(layout, Z, G, D, NM, stores):
     for kernel in (P.SJ_LPLUSTIMES, P.SJ_LTIMES_LPLUS):
         flags = P.sj_resolve(kernel, layout=layout, Z=Z, G=G, D=D, NM=NM)["flags"]
         assert flags & getattr(P, "SJ_FLAG_STORES_" + stores)
+
+
+# nm innermost: few groups of many moments by a thread per line, from 150,000 lines on
+@pytest.mark.parametrize("layout", ["ZGD", "GZD"])
+@pytest.mark.parametrize("Z,G,NM,sorted_", [(20001, 8, 16, False), (9376, 8, 16, False), (9374, 8, 16, True), (20001, 8, 15, True), (20001, 9, 16, True),
+                                            (5001, 9, 36, False), (5001, 10, 36, False), (20001, 10, 25, True), (5001, 11, 36, True), (3001, 9, 36, True)])
+def test_sorted_scattering_of_many_moments(layout, Z, G, NM, sorted_):
+    info = P.sj_resolve(P.SJ_SCATTERING, layout=layout, Z=Z, G=G, NM=NM, count=4)
+    assert bool(info["tile_k"]) == sorted_
